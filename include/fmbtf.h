@@ -114,7 +114,15 @@ typedef struct fm_stats {
                                j of the stored inverse X (0 without dense blocks) */
 } fm_stats;
 
-/* Launch schedule of a batch; zero fields take the library default. */
+/*
+ * Launch schedule of a batch; zero fields take the library default.  With no
+ * tuning, or with every field zero, small and middle-sized batches walk each
+ * (source, right-hand side) pair in one workgroup that keeps the recent values
+ * in LDS (7-point stencil, at most two rounds of workgroups, few neighbours
+ * outside that window, and at most a quarter of the free device memory for its
+ * tables and inputs); otherwise, and with any field set, the schedule is the
+ * one the fields describe.
+ */
 typedef struct fm_tuning {
     int32_t rhs_per_group;  /* right-hand sides handled by one workgroup: 1,2,4,8,16 */
     int32_t threads;        /* workgroup size: 256, 512 or 1024 (rhs groups); 256 or 512 (split) */
@@ -307,8 +315,9 @@ void fm_state_free(fm_state* st);
 /*
  * Create a batch over S states for B right-hand sides in FM_FP64 or FM_FP32
  * on the current HIP device.  Uploads the states that are not yet on the
- * device and allocates all scratch ([S][N][B] of the batch precision) so that
- * the apply calls allocate nothing.  tuning may be NULL.  hip_stream is a
+ * device and allocates all scratch ([S][N][B] of the batch precision, twice
+ * and 36 to 44 bytes per node and source where the LDS window walk is taken,
+ * fm_tuning) so that the apply calls allocate nothing.  tuning may be NULL.  hip_stream is a
  * hipStream_t (NULL: the null stream).  All states must share one grid shape.
  * Errors: FM_EINVAL, FM_ENOMEM, FM_EHIP.
  */
@@ -317,7 +326,8 @@ int fm_batch_create(fm_state* const* states, int32_t S, int32_t B, int32_t preci
 
 /*
  * Schedule search (the autotuned level chunks of the batching step, §4.4):
- * for the rhs-group kernel and every built node-split shape (threads, nodes
+ * for the LDS window walk where the default takes it (reported as a schedule
+ * of zeros), the rhs-group kernel and every built node-split shape (threads, nodes
  * per thread in flight) with 2, 4, 8 or 16 workgroups per source that fits
  * the device, create a batch of the given states, run fm_apply_J and
  * fm_apply_JT once, then time reps more pairs with HIP events on hip_stream,
@@ -345,7 +355,8 @@ int fm_autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision
 /* Change the stream later applies are enqueued on. */
 int fm_batch_set_stream(fm_batch* b, void* hip_stream);
 
-/* The schedule the batch resolved (defaults filled in). */
+/* The schedule the batch resolved (defaults filled in; with the LDS window walk
+ * the schedule its comparison baselines would take). */
 int fm_batch_tuning(const fm_batch* b, fm_tuning* out);
 
 /*
@@ -364,7 +375,8 @@ int fm_batch_tuning(const fm_batch* b, fm_tuning* out);
 int fm_batch_status(fm_batch* b);
 
 /*
- * Diagnostic of the node split: waits for the batch stream, then writes for
+ * Diagnostic of the node split (and of the LDS window walk of a batch whose
+ * schedule reports a split): waits for the batch stream, then writes for
  * every source (host xcd_masks [S]) the set of XCDs (bit i = XCD i) its
  * workgroups ran on in the last apply.  One bit per source means the
  * workgroups exchanged values through one L2 (the fast path); more bits mean

@@ -24,7 +24,7 @@ HIP_FLAGS = [
 # -ffp-contract=off keeps the setup's FP64 upwind decisions free of fused
 # multiply-adds, so they are reproducible bit for bit
 HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall", "-Wno-unused-function"]
-HIP_SOURCES = ("device.hip", "krylov.hip", "model_map.hip", "eikonal.hip", "setup_gpu.hip")
+HIP_SOURCES = ("device.hip", "ring.hip", "krylov.hip", "model_map.hip", "eikonal.hip", "setup_gpu.hip")
 # the first-arrival update and the GPU setup pass round every product and
 # sum as written (compared with a NumPy evaluation of the same formulas, and
 # with the host setup bit for bit)

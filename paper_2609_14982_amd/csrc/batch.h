@@ -9,6 +9,8 @@
 
 namespace fm {
 
+struct RingPlan;   // LDS-window walk of a batch (ring.h)
+
 // An off-grid point source (Section 3.1 source-seed rows, the direct term of
 // eq. (source-jacobian)); a state whose source sits on a node has none.
 struct PtDev {
@@ -126,6 +128,7 @@ struct fm_batch {
     int32_t max_seed = 0, max_tgt = 0;
     void* union_blob = nullptr;      // UnionDev arrays (J^T summed)
     fm::UnionDev uni{};
+    fm::RingPlan* ring = nullptr;    // LDS-window walk, run in place of the other kernels when set
 };
 
 namespace fm {

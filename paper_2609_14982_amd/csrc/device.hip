@@ -27,6 +27,7 @@
 #include <vector>
 
 #include "batch.h"
+#include "ring.h"
 
 namespace fm {
 
@@ -992,6 +993,11 @@ static int prepare_point_sources(fm_batch* b) {
     return FM_OK;
 }
 
+static bool is_default(const fm_tuning& t) {
+    return t.rhs_per_group == 0 && t.threads == 0 && t.min_lds_bytes == 0 && t.xcd_aware == 0 && t.unroll == 0 &&
+           t.split == 0 && t.balance == 0;
+}
+
 int batch_create(fm_state* const* states, int32_t S, int32_t B, int32_t precision, const fm_tuning* tuning,
                  void* stream, fm_batch** out) {
     if (!out) { set_error("null output pointer"); return FM_EINVAL; }
@@ -1114,6 +1120,8 @@ int batch_create(fm_state* const* states, int32_t S, int32_t B, int32_t precisio
         return e == hipErrorOutOfMemory ? FM_ENOMEM : FM_EHIP;
     }
     rc = prepare_point_sources(b);
+    // a caller's own schedule is taken as asked; the window walk is a default
+    if (rc == FM_OK && (!tuning || is_default(*tuning))) rc = ring_create(b, h, &b->ring);
     if (rc) {
         batch_free(b);
         return rc;
@@ -1132,6 +1140,7 @@ void batch_free(fm_batch* b) {
     if (b->d_src) (void)hipFree(b->d_src);
     if (b->scratch) (void)hipFree(b->scratch);
     if (b->union_blob) (void)hipFree(b->union_blob);
+    ring_free(b->ring);
     delete b;
 }
 
@@ -1196,7 +1205,8 @@ int apply_J(fm_batch* b, const void* ds, int32_t ds_mode, void* out, int32_t out
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) { set_error("seed-row launch failed: %s", hipGetErrorString(e)); return FM_EHIP; }
     }
-    hipError_t e = b->tun.split > 1       ? launch_split(b, true, a)
+    hipError_t e = ring_has(b->ring, true) ? ring_walk(b, true, a)
+                   : b->tun.split > 1     ? launch_split(b, true, a)
                    : b->prec == FM_FP64 ? launch_sweep<double>(true, b->tun, a, b->grid, b->lds_bytes, b->stream)
                                         : launch_sweep<float>(true, b->tun, a, b->grid, b->lds_bytes, b->stream);
     if (e != hipSuccess) { set_error("forward launch failed: %s", hipGetErrorString(e)); return FM_EHIP; }
@@ -1226,7 +1236,8 @@ int apply_JT(fm_batch* b, const void* w, int32_t w_mode, void* out, int32_t out_
     a.out = out;
     a.work = b->scratch;
     a.xB = b->xB;
-    hipError_t e = b->tun.split > 1       ? launch_split(b, false, a)
+    hipError_t e = ring_has(b->ring, false) ? ring_walk(b, false, a)
+                   : b->tun.split > 1     ? launch_split(b, false, a)
                    : b->prec == FM_FP64 ? launch_sweep<double>(false, b->tun, a, b->grid, b->lds_bytes, b->stream)
                                         : launch_sweep<float>(false, b->tun, a, b->grid, b->lds_bytes, b->stream);
     if (e != hipSuccess) { set_error("reverse launch failed: %s", hipGetErrorString(e)); return FM_EHIP; }
@@ -1605,6 +1616,7 @@ int autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision, v
         }
     }
     std::vector<fm_tuning> list;
+    list.push_back(fm_tuning{});                      // the window walk, where the library takes it
     list.push_back(fm_tuning{0, 0, 0, 0, 0, 1, 0});   // rhs groups, library defaults
     const int vw = precision == FM_FP64 ? 2 : 4;
     const int lpn = B % vw == 0 ? B / vw : 0;
@@ -1637,6 +1649,7 @@ int autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision, v
         fm_batch* b = nullptr;
         if (batch_create(states, S, B, precision, &t, stream, &b) != FM_OK) continue;   // does not fit
         if (t.split > 1 && !t.balance && b->tun.split != t.split) { batch_free(b); continue; }
+        if (is_default(t) && !b->ring) { batch_free(b); continue; }   // one of the schedules below
         float m = -1.0f;
         rc = apply_J(b, ds, ds_mode, j_out, out_mode);
         if (rc == FM_OK) rc = apply_JT(b, w, w_mode, jt_out, jt_mode);
@@ -1650,7 +1663,7 @@ int autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision, v
                 m /= (float)reps;
         }
         if (rc == FM_OK) rc = batch_status(b);
-        const fm_tuning used = b->tun;
+        const fm_tuning used = b->ring ? t : b->tun;   // zero fields ask for the window walk again
         batch_free(b);
         if (rc != FM_OK) break;
         if (m >= 0.0f) {
