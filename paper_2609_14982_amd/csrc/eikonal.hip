@@ -23,10 +23,10 @@
 // (a source on a node is the case of integer xi).
 //
 // Work per iteration: a node is recomputed only when a neighbour changed in
-// the previous iteration (one state byte per node and source: changed, seed);
-// the others keep their value, which the buffer being written already holds
-// unless the node changed in the previous iteration.  The per-iteration
-// "anything changed" flags are read by the host once per chunk of iterations.  Built with
+// the previous iteration (one bit per node and source, the word of 64 nodes the
+// unit); the others keep their value, which the buffer being written already
+// holds unless the node changed in the previous iteration.  The per-iteration
+// amount of work of each is read by the host once per chunk of iterations.  Built with
 // -ffp-contract=off: every product and sum is rounded as written.
 #include <hip/hip_runtime.h>
 
@@ -45,12 +45,19 @@ struct fm_eikonal {
     int32_t S = 0;                  // capacity in sources
     double* X = nullptr;            // device [N][dim]
     double* Tb = nullptr;           // device [S][N] second buffer
-    uint8_t* st[2] = {nullptr, nullptr};   // device [S][N] node states
+    int64_t W = 0;                  // words of 64 nodes per source (a multiple of kTile)
+    uint16_t* list = nullptr;       // device [S][W / 64][4096] nodes of a tile to recompute
+    int32_t* count = nullptr;       // device [S][W / 64] their number
+    uint32_t* batch = nullptr;      // device [S][W] batches of 64 of them: tile * 64 + batch
+    uint64_t* chg[2] = {nullptr, nullptr};   // device [S][W] nodes changed by the last iteration
+    uint64_t* seed = nullptr;       // device [S][W] seed nodes
+    uint64_t* edge = nullptr;       // device [4][W] nodes with a lower / upper neighbour on axes 0 and 1
     double* xi = nullptr;           // device [S][3]
-    unsigned* flags = nullptr;      // device [kChunk]
-    unsigned* flags_h = nullptr;    // pinned host [kChunk]
+    unsigned* n_batch = nullptr;    // device [kChunk + 1] batches of each iteration of a chunk and the next
+    unsigned* n_batch_h = nullptr;  // pinned host copy
     hipStream_t stream = nullptr;
     int device = -1;
+    int waves = 0;                  // waves of an iteration's recomputation
 };
 
 namespace fm {
@@ -58,11 +65,13 @@ namespace fm {
 namespace {
 
 constexpr int kChunk = 16;          // iterations between convergence checks
-constexpr uint8_t kChanged = 1, kSeed = 2;
+constexpr int kTile = 64;           // words of 64 nodes listed by one wave
+constexpr int kThreads = 256;
+constexpr uint16_t kCopy = 1u << 15;   // list entry: the value is only copied
 
 struct EikDims {
     int dim;
-    int64_t n0, n1, n2, N;
+    int64_t n0, n1, n2, N, W;
 };
 
 __device__ __forceinline__ void logical(const EikDims& d, int64_t p, int64_t c[3]) {
@@ -137,23 +146,30 @@ __device__ __forceinline__ double tri_inner(const double* xi, double si, const d
 }
 
 // Seeds and +inf in both buffers (an iteration leaves a node's value in the
-// buffer it writes untouched when that buffer already holds it): one thread
-// per (source, node).
-__global__ void k_eik_init(EikDims d, int32_t S, const double* __restrict__ X, const double* __restrict__ s,
-                           const double* __restrict__ xi, double rho, double* __restrict__ T,
-                           double* __restrict__ T2, uint8_t* __restrict__ st) {
-    const int64_t total = (int64_t)S * d.N;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t alpha = t / d.N, p = t - alpha * d.N;
+// buffer it writes untouched when that buffer already holds it), and the seeds
+// as the nodes changed last: one wave per word, one lane per node.
+__global__ __launch_bounds__(kThreads) void k_eik_init(EikDims d, int32_t S, const double* __restrict__ X,
+                                                       const double* __restrict__ s, const double* __restrict__ xi,
+                                                       double rho, double* __restrict__ T, double* __restrict__ T2,
+                                                       uint64_t* __restrict__ chg, uint64_t* __restrict__ seeds) {
+    const int64_t total = (int64_t)S * d.W;
+    for (int64_t i = (blockIdx.x * (int64_t)kThreads + threadIdx.x) / 64; i < total; i += (int64_t)gridDim.x * (kThreads / 64)) {
+        const int64_t alpha = i / d.W, p = (i - alpha * d.W) * 64 + (threadIdx.x & 63);
+        const int64_t t = alpha * d.N + p;
         const double* xs = xi + alpha * 3;
         int64_t c[3];
         logical(d, p, c);
-        bool seed = true;
+        bool seed = p < d.N;
         for (int k = 0; k < d.dim; ++k) seed = seed && fabs((double)c[k] - xs[k]) <= rho;
+        const uint64_t word = __ballot(seed);
+        if ((threadIdx.x & 63) == 0) {
+            chg[i] = word;
+            seeds[i] = word;
+        }
+        if (p >= d.N) continue;
         if (!seed) {
             T[t] = INFINITY;
             T2[t] = INFINITY;
-            st[t] = 0;
             continue;
         }
         // the source's cell: corners and multilinear weights
@@ -183,87 +199,189 @@ __global__ void k_eik_init(EikDims d, int32_t S, const double* __restrict__ X, c
         const double v = 0.5 * (s_src + s[p]) * dist(X + p * d.dim, x_src, d.dim);
         T[t] = v;
         T2[t] = v;
-        st[t] = kSeed | kChanged;
     }
 }
 
-__global__ void k_clear_flags(unsigned* f) {
-    if (threadIdx.x < kChunk) f[threadIdx.x] = 0u;
-}
-
-// One Jacobi iteration for every (source, node).
-template <int DIM>
-__global__ void k_eik_step(EikDims d, int32_t S, const double* __restrict__ X, const double* __restrict__ s,
-                           const double* __restrict__ Told, double* __restrict__ Tnew,
-                           const uint8_t* __restrict__ sold, uint8_t* __restrict__ snew, unsigned* flag) {
-    const int64_t total = (int64_t)S * d.N;
-    const int64_t stride[3] = {1, d.n0, d.n0 * d.n1};
-    const int64_t nn[3] = {d.n0, d.n1, d.n2};
-    int any = 0;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t alpha = t / d.N, p = t - alpha * d.N;
-        const int64_t row = alpha * d.N;
-        const uint8_t me = sold[t];
-        if (me & kSeed) {
-            snew[t] = kSeed;
-            continue;
-        }
+// Nodes with a lower and an upper neighbour on axes 0 and 1 (the last axis
+// needs none: its shifts leave the grid).
+__global__ __launch_bounds__(kThreads) void k_eik_edges(EikDims d, uint64_t* __restrict__ edge) {
+    for (int64_t i = (blockIdx.x * (int64_t)kThreads + threadIdx.x) / 64; i < d.W; i += (int64_t)gridDim.x * (kThreads / 64)) {
+        const int64_t p = i * 64 + (threadIdx.x & 63);
         int64_t c[3];
         logical(d, p, c);
-        int64_t nb[DIM][2];
-        bool act = false;
-        for (int k = 0; k < DIM; ++k) {
-            nb[k][0] = c[k] > 0 ? p - stride[k] : -1;
-            nb[k][1] = c[k] < nn[k] - 1 ? p + stride[k] : -1;
-            for (int side = 0; side < 2; ++side)
-                if (nb[k][side] >= 0) act = act || (sold[row + nb[k][side]] & kChanged);
-        }
-        if (!act) {
-            // T^{n+1} = T^n; the buffer written now holds T^{n-1}, which is
-            // the same value unless the node changed in the last iteration
-            if (me & kChanged) Tnew[t] = Told[t];
-            snew[t] = 0;
-            continue;
-        }
-        const double told = Told[t];
-        double v = told;
-        {
-            const double si = s[p];
-            double xi[3], xk[DIM][2][3], tk[DIM][2];
-            for (int k = 0; k < DIM; ++k) xi[k] = X[p * DIM + k];
-            double best = INFINITY;
-            for (int k = 0; k < DIM; ++k)
-                for (int side = 0; side < 2; ++side) {
-                    const int64_t q = nb[k][side];
-                    tk[k][side] = q >= 0 ? Told[row + q] : INFINITY;
-                    for (int m = 0; m < DIM; ++m) xk[k][side][m] = q >= 0 ? X[q * DIM + m] : 0.0;
-                    if (q >= 0) best = fmin(best, tk[k][side] + si * dist(xi, xk[k][side], DIM));
-                }
-            // a simplex whose vertex values are all >= best cannot lower it:
-            // its interior values exceed its least vertex value
-            for (int a = 0; a < DIM; ++a)
-                for (int b = a + 1; b < DIM; ++b)
-                    for (int sa = 0; sa < 2; ++sa)
-                        for (int sb = 0; sb < 2; ++sb)
-                            if (nb[a][sa] >= 0 && nb[b][sb] >= 0 && fmin(tk[a][sa], tk[b][sb]) < best)
-                                best = fmin(best, seg_inner(xi, si, xk[a][sa], tk[a][sa], xk[b][sb], tk[b][sb], DIM));
-            if constexpr (DIM == 3) {
-                for (int s0 = 0; s0 < 2; ++s0)
-                    for (int s1 = 0; s1 < 2; ++s1)
-                        for (int s2 = 0; s2 < 2; ++s2)
-                            if (nb[0][s0] >= 0 && nb[1][s1] >= 0 && nb[2][s2] >= 0 &&
-                                fmin(fmin(tk[0][s0], tk[1][s1]), tk[2][s2]) < best)
-                                best = fmin(best, tri_inner(xi, si, xk[0][s0], tk[0][s0], xk[1][s1], tk[1][s1],
-                                                            xk[2][s2], tk[2][s2]));
-            }
-            v = fmin(told, best);
-        }
-        Tnew[t] = v;
-        const bool ch = v != told;
-        snew[t] = ch ? kChanged : 0;
-        any |= ch ? 1 : 0;
+        const bool in = p < d.N;
+        const uint64_t w[4] = {__ballot(in && c[0] > 0), __ballot(in && c[0] < d.n0 - 1), __ballot(in && c[1] > 0),
+                               __ballot(in && c[1] < d.n1 - 1)};
+        if ((threadIdx.x & 63) == 0)
+            for (int k = 0; k < 4; ++k) edge[k * d.W + i] = w[k];
     }
-    if (__syncthreads_or(any) && threadIdx.x == 0) atomicOr(flag, 1u);
+}
+
+__global__ void k_clear_counts(unsigned* f) {
+    if (threadIdx.x <= kChunk) f[threadIdx.x] = 0u;
+}
+
+// Word i of the mask m [W] shifted so that bit p holds bit p - off.
+__device__ __forceinline__ uint64_t shifted(const uint64_t* __restrict__ m, int64_t i, int64_t W, int64_t off) {
+    const int64_t bit = i * 64 - off;              // source bit of bit 0 of the result
+    const int64_t lo = bit >> 6;                   // (rounds towards minus infinity)
+    const int sh = (int)(bit & 63);
+    const uint64_t a = lo >= 0 && lo < W ? m[lo] : 0ull;
+    if (sh == 0) return a;
+    const uint64_t b = lo + 1 >= 0 && lo + 1 < W ? m[lo + 1] : 0ull;
+    return a >> sh | b << (64 - sh);
+}
+
+// An iteration is two launches.  The first spreads the changed bits to their
+// face neighbours (a few words per 64 nodes) and lists the nodes to recompute,
+// one wave per tile of 64 words: the tile's nodes in order, and a batch for
+// every 64 of them, so that the second launch finds all its work in full waves
+// wherever the front is.
+// With one lane per node and a state byte each, an iteration of 8 sources on
+// 101x101x51 took 212 us, front or not; now 11 us and 57 us.  With each
+// workgroup listing and recomputing its own 1024 nodes it was 95 us (with 512
+// nodes 120, with 256 183: the workgroups away from the front, each of which
+// only reads its words, took the time).  Neither kernel updates a word that
+// every wave shares: those updates queue, 10 ns each (a counter that dealt out
+// the batches cost 40 us, one flag set by every wave 15 us).
+template <int DIM>
+__global__ __launch_bounds__(kThreads) void k_eik_list(EikDims d, int32_t S, const uint64_t* __restrict__ cold,
+                                                       uint64_t* __restrict__ cnew, const uint64_t* __restrict__ seeds,
+                                                       const uint64_t* __restrict__ edge, uint16_t* __restrict__ list,
+                                                       int32_t* __restrict__ count, uint32_t* __restrict__ batch,
+                                                       unsigned* __restrict__ n_batch) {
+    __shared__ unsigned wave_n[kThreads / 64], wave_at;
+    const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+    const int64_t tiles = (int64_t)S * (d.W / kTile);
+    for (int64_t t0 = blockIdx.x * (int64_t)(kThreads / 64); t0 < tiles; t0 += (int64_t)gridDim.x * (kThreads / 64)) {
+        const int64_t tile = t0 + wave;
+        int total = 0;
+        if (tile < tiles) {
+            const int64_t alpha = tile / (d.W / kTile), i = (tile - alpha * (d.W / kTile)) * kTile + lane;
+            const uint64_t* __restrict__ co = cold + alpha * d.W;
+            uint64_t a = (shifted(co, i, d.W, 1) & edge[i]) | (shifted(co, i, d.W, -1) & edge[d.W + i]) |
+                         (shifted(co, i, d.W, d.n0) & edge[2 * d.W + i]) | (shifted(co, i, d.W, -d.n0) & edge[3 * d.W + i]);
+            if (DIM == 3) a |= shifted(co, i, d.W, d.n0 * d.n1) | shifted(co, i, d.W, -d.n0 * d.n1);
+            const int64_t left = d.N - i * 64;
+            if (left < 64) a &= left > 0 ? (1ull << left) - 1ull : 0ull;
+            const uint64_t open = ~seeds[alpha * d.W + i];
+            a &= open;
+            const uint64_t t = a | (co[i] & open);
+            cnew[alpha * d.W + i] = 0ull;
+            int n = __popcll(t);       // running sum over the lanes
+            for (int o = 1; o < 64; o <<= 1) {
+                const int x = __shfl_up(n, o);
+                if (lane >= o) n += x;
+            }
+            total = __shfl(n, 63);
+            uint16_t* __restrict__ out = list + tile * (kTile * 64);
+            for (uint64_t m = __ballot(t != 0ull); m; m &= m - 1ull) {
+                const int w = __ffsll((unsigned long long)m) - 1;
+                const uint64_t tw = __shfl((unsigned long long)t, w), aw = __shfl((unsigned long long)a, w);
+                const int end = __shfl(n, w);
+                if (tw >> lane & 1ull)
+                    out[end - __popcll(tw >> lane)] = (uint16_t)(w * 64 + lane) | (aw >> lane & 1ull ? (uint16_t)0 : kCopy);
+            }
+        }
+        // places for the batches of the whole workgroup at once: one atomic on
+        // the counter (from every wave of the card they queue, 10 ns each)
+        const int nb = (total + 63) / 64;
+        if (lane == 0) wave_n[wave] = (unsigned)nb;
+        __syncthreads();
+        unsigned before = 0u, all = 0u;
+        for (int w = 0; w < kThreads / 64; ++w) {
+            before += w < wave ? wave_n[w] : 0u;
+            all += wave_n[w];
+        }
+        if (all && threadIdx.x == 0) wave_at = atomicAdd(n_batch, all);
+        __syncthreads();
+        if (total && lane == 0) count[tile] = total;
+        if (lane < nb) batch[wave_at + before + lane] = (uint32_t)(tile * kTile + lane);
+    }
+}
+
+// The listed nodes, one per lane.  Bound by the FP64 divisions and square
+// roots (divergent: simplices that cannot lower the value are skipped) and
+// their registers (three waves per SIMD in 3-D).
+template <int DIM>
+__global__ __launch_bounds__(64, 3) void k_eik_step(EikDims d, const double* __restrict__ X,
+                                                 const double* __restrict__ s, const double* __restrict__ Told_,
+                                                 double* __restrict__ Tnew_, unsigned long long* __restrict__ cnew,
+                                                 const uint16_t* __restrict__ list, const int32_t* __restrict__ count,
+                                                 const uint32_t* __restrict__ batch, const unsigned* __restrict__ n_batch) {
+    __shared__ unsigned long long ch[kTile];           // changed nodes of the batch's tile
+    const int lane = (int)threadIdx.x;
+    const uint32_t n0 = (uint32_t)d.n0, n1 = (uint32_t)d.n1, n2 = (uint32_t)d.n2;
+    const int64_t stride[3] = {1, d.n0, d.n0 * d.n1};
+    const uint32_t nn[3] = {n0, n1, n2};
+    const uint32_t tps = (uint32_t)(d.W / kTile);      // tiles per source
+    const unsigned n_b = *n_batch;
+    ch[lane] = 0ull;
+    for (unsigned at = blockIdx.x; at < n_b; at += gridDim.x) {
+        const uint32_t e = batch[at], tile = e / kTile;
+        const int32_t k = (int32_t)(e - tile * kTile) * 64 + lane;
+        const uint32_t alpha = tile / tps;
+        if (k < count[tile]) {
+            const uint32_t entry = list[(size_t)tile * (kTile * 64) + k];
+            const uint32_t p32 = (tile - alpha * tps) * (kTile * 64) + (entry & (kCopy - 1u));
+            const int64_t p = p32;
+            const double* __restrict__ Told = Told_ + alpha * d.N;
+            double* __restrict__ Tnew = Tnew_ + alpha * d.N;
+            if (entry & kCopy) {
+                // T^{n+1} = T^n; the buffer written now holds T^{n-1}, which is
+                // the same value unless the node changed in the last iteration
+                Tnew[p] = Told[p];
+            } else {
+                const uint32_t r = p32 / n0;
+                const uint32_t c[3] = {p32 - r * n0, r % n1, r / n1};
+                int64_t nb[DIM][2];
+                for (int k = 0; k < DIM; ++k) {
+                    nb[k][0] = c[k] > 0 ? p - stride[k] : -1;
+                    nb[k][1] = c[k] < nn[k] - 1 ? p + stride[k] : -1;
+                }
+                const double told = Told[p];
+                const double si = s[p];
+                double xi[3], xk[DIM][2][3], tk[DIM][2];
+                for (int k = 0; k < DIM; ++k) xi[k] = X[p * DIM + k];
+                double best = INFINITY;
+                for (int k = 0; k < DIM; ++k)
+                    for (int side = 0; side < 2; ++side) {
+                        const int64_t q = nb[k][side];
+                        tk[k][side] = q >= 0 ? Told[q] : INFINITY;
+                        for (int m = 0; m < DIM; ++m) xk[k][side][m] = q >= 0 ? X[q * DIM + m] : 0.0;
+                        if (q >= 0) best = fmin(best, tk[k][side] + si * dist(xi, xk[k][side], DIM));
+                    }
+                // a simplex whose vertex values are all >= best cannot lower it:
+                // its interior values exceed its least vertex value
+                for (int a = 0; a < DIM; ++a)
+                    for (int b = a + 1; b < DIM; ++b)
+                        for (int sa = 0; sa < 2; ++sa)
+                            for (int sb = 0; sb < 2; ++sb)
+                                if (nb[a][sa] >= 0 && nb[b][sb] >= 0 && fmin(tk[a][sa], tk[b][sb]) < best)
+                                    best = fmin(best, seg_inner(xi, si, xk[a][sa], tk[a][sa], xk[b][sb], tk[b][sb], DIM));
+                if constexpr (DIM == 3) {
+                    for (int s0 = 0; s0 < 2; ++s0)
+                        for (int s1 = 0; s1 < 2; ++s1)
+                            for (int s2 = 0; s2 < 2; ++s2)
+                                if (nb[0][s0] >= 0 && nb[1][s1] >= 0 && nb[2][s2] >= 0 &&
+                                    fmin(fmin(tk[0][s0], tk[1][s1]), tk[2][s2]) < best)
+                                    best = fmin(best, tri_inner(xi, si, xk[0][s0], tk[0][s0], xk[1][s1], tk[1][s1],
+                                                                xk[2][s2], tk[2][s2]));
+                }
+                const double v = fmin(told, best);
+                Tnew[p] = v;
+                if (v != told) atomicOr(&ch[p32 >> 6 & (kTile - 1)], 1ull << (p32 & 63u));
+            }
+        }
+        // one global update per changed word (a wave's own LDS order is program order)
+        __syncthreads();
+        const unsigned long long m = ch[lane];
+        if (m) {
+            atomicOr(cnew + alpha * d.W + (size_t)(tile - alpha * tps) * kTile + lane, m);
+            ch[lane] = 0ull;
+        }
+        __syncthreads();
+    }
 }
 
 }  // namespace
@@ -300,12 +418,28 @@ int fm_eikonal_create(int32_t dim, int64_t n1, int64_t n2, int64_t n3, const dou
     const size_t nsn = (size_t)max_sources * (size_t)N;
     if (h == hipSuccess) h = hipMalloc(&e->X, sizeof(double) * (size_t)N * dim);
     if (h == hipSuccess) h = hipMalloc(&e->Tb, sizeof(double) * nsn);
-    if (h == hipSuccess) h = hipMalloc(&e->st[0], nsn);
-    if (h == hipSuccess) h = hipMalloc(&e->st[1], nsn);
+    e->W = (N + 64 * kTile - 1) / (64 * kTile) * kTile;
+    const size_t words = sizeof(uint64_t) * (size_t)max_sources * (size_t)e->W;
+    if (h == hipSuccess) h = hipMalloc(&e->chg[0], words);
+    if (h == hipSuccess) h = hipMalloc(&e->chg[1], words);
+    if (h == hipSuccess) h = hipMalloc(&e->seed, words);
+    if (h == hipSuccess) h = hipMalloc(&e->edge, sizeof(uint64_t) * 4 * (size_t)e->W);
+    if (h == hipSuccess) h = hipMalloc(&e->list, sizeof(uint16_t) * 64 * (size_t)max_sources * (size_t)e->W);
+    if (h == hipSuccess) h = hipMalloc(&e->count, sizeof(int32_t) * (size_t)max_sources * (size_t)(e->W / kTile));
+    if (h == hipSuccess) h = hipMalloc(&e->batch, sizeof(uint32_t) * (size_t)max_sources * (size_t)e->W);
+    int cus = 0;
+    if (h == hipSuccess) h = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, e->device);
+    e->waves = cus * 24;    // 12 a CU are resident; more for the batches' different lengths
     if (h == hipSuccess) h = hipMalloc(&e->xi, sizeof(double) * 3 * (size_t)max_sources);
-    if (h == hipSuccess) h = hipMalloc(&e->flags, sizeof(unsigned) * kChunk);
-    if (h == hipSuccess) h = hipHostMalloc((void**)&e->flags_h, sizeof(unsigned) * kChunk, hipHostMallocDefault);
+    if (h == hipSuccess) h = hipMalloc(&e->n_batch, sizeof(unsigned) * (kChunk + 1));
+    if (h == hipSuccess) h = hipHostMalloc((void**)&e->n_batch_h, sizeof(unsigned) * (kChunk + 1), hipHostMallocDefault);
     if (h == hipSuccess) h = hipMemcpy(e->X, X, sizeof(double) * (size_t)N * dim, hipMemcpyHostToDevice);
+    if (h == hipSuccess) {
+        hipLaunchKernelGGL(k_eik_edges, dim3((unsigned)std::min<int64_t>((e->W + 3) / 4, 4096)), dim3(kThreads), 0, nullptr,
+                           EikDims{e->dim, e->n[0], e->n[1], e->n[2], e->N, e->W}, e->edge);
+        h = hipGetLastError();
+        if (h == hipSuccess) h = hipStreamSynchronize(nullptr);
+    }
     if (h != hipSuccess) {
         set_error("first-arrival solver allocation failed: %s", hipGetErrorString(h));
         fm_eikonal_free(e);
@@ -355,32 +489,36 @@ int fm_eikonal_solve(fm_eikonal* e, const double* s, int32_t S, const double* xi
     }
     hipStream_t st = e->stream;
     HIP_TRY(hipMemcpyAsync(e->xi, xi.data(), sizeof(double) * xi.size(), hipMemcpyHostToDevice, st));
-    EikDims d{e->dim, e->n[0], e->n[1], e->n[2], e->N};
+    EikDims d{e->dim, e->n[0], e->n[1], e->n[2], e->N, e->W};
     const int64_t total = (int64_t)S * e->N;
-    const int grid = (int)std::min<int64_t>((total + 255) / 256, 16384);
+    const int grid = (int)std::min<int64_t>(((int64_t)S * e->W + 3) / 4, 16384);
+    const int tiles = (int)std::min<int64_t>(((int64_t)S * (e->W / kTile) + 3) / 4, 16384);
     double* buf[2] = {T, e->Tb};
     hipLaunchKernelGGL(k_eik_init, dim3(grid), dim3(256), 0, st, d, S, e->X, s, e->xi, seed_radius, buf[0], buf[1],
-                       e->st[0]);
+                       e->chg[0], e->seed);
     HIP_TRY(hipGetLastError());
     int cur = 0;
     int32_t done = 0;
     while (done < max_iter) {
         const int n = std::min<int32_t>(kChunk, max_iter - done);
-        hipLaunchKernelGGL(k_clear_flags, dim3(1), dim3(64), 0, st, e->flags);
-        for (int j = 0; j < n; j++) {
-            if (e->dim == 3)
-                hipLaunchKernelGGL(k_eik_step<3>, dim3(grid), dim3(256), 0, st, d, S, e->X, s, buf[cur], buf[cur ^ 1],
-                                   e->st[cur], e->st[cur ^ 1], e->flags + j);
-            else
-                hipLaunchKernelGGL(k_eik_step<2>, dim3(grid), dim3(256), 0, st, d, S, e->X, s, buf[cur], buf[cur ^ 1],
-                                   e->st[cur], e->st[cur ^ 1], e->flags + j);
+        hipLaunchKernelGGL(k_clear_counts, dim3(1), dim3(64), 0, st, e->n_batch);
+        const auto list_fn = e->dim == 3 ? k_eik_list<3> : k_eik_list<2>;
+        const auto step_fn = e->dim == 3 ? k_eik_step<3> : k_eik_step<2>;
+        // an iteration changed nothing when the next list is empty: one more
+        // list follows the chunk (its iteration lists the same again)
+        for (int j = 0; j <= n; j++) {
+            hipLaunchKernelGGL(list_fn, dim3(tiles), dim3(kThreads), 0, st, d, S, e->chg[cur], e->chg[cur ^ 1],
+                               e->seed, e->edge, e->list, e->count, e->batch, e->n_batch + j);
+            if (j == n) break;
+            hipLaunchKernelGGL(step_fn, dim3(e->waves), dim3(64), 0, st, d, e->X, s, buf[cur], buf[cur ^ 1],
+                               (unsigned long long*)e->chg[cur ^ 1], e->list, e->count, e->batch, e->n_batch + j);
             cur ^= 1;
         }
         HIP_TRY(hipGetLastError());
-        HIP_TRY(hipMemcpyAsync(e->flags_h, e->flags, sizeof(unsigned) * n, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(e->n_batch_h, e->n_batch, sizeof(unsigned) * (n + 1), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         for (int j = 0; j < n; j++) {
-            if (!e->flags_h[j]) {
+            if (!e->n_batch_h[j + 1]) {
                 // iteration done + j + 1 changed nothing; the later ones of the
                 // chunk left the same values in the buffer now current
                 if (iterations) *iterations = done + j + 1;
@@ -403,11 +541,16 @@ void fm_eikonal_free(fm_eikonal* e) {
     if (!e) return;
     if (e->X) (void)hipFree(e->X);
     if (e->Tb) (void)hipFree(e->Tb);
-    if (e->st[0]) (void)hipFree(e->st[0]);
-    if (e->st[1]) (void)hipFree(e->st[1]);
+    if (e->chg[0]) (void)hipFree(e->chg[0]);
+    if (e->chg[1]) (void)hipFree(e->chg[1]);
+    if (e->seed) (void)hipFree(e->seed);
+    if (e->edge) (void)hipFree(e->edge);
+    if (e->list) (void)hipFree(e->list);
+    if (e->count) (void)hipFree(e->count);
+    if (e->batch) (void)hipFree(e->batch);
     if (e->xi) (void)hipFree(e->xi);
-    if (e->flags) (void)hipFree(e->flags);
-    if (e->flags_h) (void)hipHostFree(e->flags_h);
+    if (e->n_batch) (void)hipFree(e->n_batch);
+    if (e->n_batch_h) (void)hipHostFree(e->n_batch_h);
     delete e;
 }
 
