@@ -44,45 +44,132 @@ __device__ __forceinline__ void cell_range(int64_t i, int64_t n, int64_t& lo, in
     hi = i < n - 1 ? i : n - 2;
 }
 
-template <typename V>
-__global__ void k_model_map(MapDims d, const double* __restrict__ a, const V* __restrict__ dv, V* __restrict__ ds,
-                            int B) {
-    const int64_t total = d.n0 * d.n1 * d.n2 * B;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t p = t / B, b = t - p * B;
-        const int64_t i = p % d.n0, r = p / d.n0, j = r % d.n1, k = r / d.n1;
-        int64_t i0, i1, j0, j1, k0, k1;
+// VW right-hand sides of one row: 16 bytes where rows and pointers allow it.
+template <typename V, int VW>
+struct alignas(sizeof(V) * VW) Row {
+    V v[VW];
+};
+
+// Both products are bound by the rows they move (each input row read from
+// memory once, each output row written once) as long as the indices cost
+// little: a thread takes VW right-hand sides of a column of kc planes of the
+// last axis, so that it splits its index once for the column and reads a plane
+// once for the two outputs that share it.  The sums stay in ascending order:
+// the plane's own sum, needed first by the next output, is formed beside the
+// output that continues the previous plane's.  201x201x101, 16 right-hand
+// sides, FP64: 680 us (M) and 691 us (M^T) with one thread per output value,
+// eight loads and five 64-bit divisions each.
+template <typename V, int VW>
+__global__ __launch_bounds__(256) void k_model_map(MapDims d, const double* __restrict__ a, const V* __restrict__ dv,
+                                                   V* __restrict__ ds, int B, int kc) {
+    typedef Row<V, VW> R;
+    const int64_t L = B / VW, total = d.n0 * d.n1 * L;
+    const R* __restrict__ in = (const R*)dv;
+    R* __restrict__ out = (R*)ds;
+    for (int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+        const int64_t r = t / L, col = t - r * L, j = r / d.n0, i = r - j * d.n0;
+        int64_t i0, i1, j0, j1;
         cell_range(i, d.n0, i0, i1);
         cell_range(j, d.n1, j0, j1);
-        cell_range(k, d.n2, k0, k1);
-        V acc = (V)0;
-        for (int64_t ck = k0; ck <= k1; ++ck)
-            for (int64_t cj = j0; cj <= j1; ++cj)
-                for (int64_t ci = i0; ci <= i1; ++ci) acc += dv[(ci + d.c0 * (cj + d.c1 * ck)) * B + b];
-        ds[t] = (V)a[p] * acc;
+        const bool two_i = i1 > i0, two_j = j1 > j0;
+        const int64_t plane = d.c0 * d.c1 * L, di = L, dj = d.c0 * L;
+        const R* __restrict__ base = in + (i0 + d.c0 * j0) * L + col;
+        auto add = [](R& x, const R& y) {
+#pragma unroll
+            for (int v = 0; v < VW; ++v) x.v[v] += y.v[v];
+        };
+        // acc continues with plane ck, own starts with it
+        auto cells = [&](int64_t ck, R& acc, R& own) {
+            const R* __restrict__ x = base + ck * plane;
+            R y[4];
+            y[0] = x[0];
+            if (two_i) y[1] = x[di];
+            if (two_j) {
+                y[2] = x[dj];
+                if (two_i) y[3] = x[dj + di];
+            }
+            own = R{};
+            add(acc, y[0]);
+            add(own, y[0]);
+            if (two_i) { add(acc, y[1]); add(own, y[1]); }
+            if (two_j) {
+                add(acc, y[2]);
+                add(own, y[2]);
+                if (two_i) { add(acc, y[3]); add(own, y[3]); }
+            }
+        };
+        for (int64_t k0 = (int64_t)blockIdx.y * kc; k0 < d.n2; k0 += (int64_t)gridDim.y * kc) {
+            const int64_t k1 = k0 + kc < d.n2 ? k0 + kc : d.n2;
+            R acc{}, own{};
+            if (k0 > 0) cells(k0 - 1, acc, own);
+            for (int64_t k = k0; k < k1; ++k) {
+                acc = own;
+                if (k < d.c2) cells(k, acc, own);
+                const int64_t p = i + d.n0 * (j + d.n1 * k);
+                const V c = (V)a[p];
+                R o;
+#pragma unroll
+                for (int v = 0; v < VW; ++v) o.v[v] = c * acc.v[v];
+                out[p * L + col] = o;
+            }
+        }
     }
 }
 
-template <typename V>
-__global__ void k_model_map_t(MapDims d, const double* __restrict__ a, const V* __restrict__ g, V* __restrict__ out,
-                              int B) {
-    const int64_t total = d.c0 * d.c1 * d.c2 * B;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < total; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = t / B, b = t - c * B;
-        const int64_t ci = c % d.c0, r = c / d.c0, cj = r % d.c1, ck = r / d.c1;
-        const int64_t i1 = d.n0 > 1 ? ci + 1 : ci, j1 = d.n1 > 1 ? cj + 1 : cj, k1 = d.n2 > 1 ? ck + 1 : ck;
-        V acc = (V)0;
-        for (int64_t k = ck; k <= k1; ++k)
-            for (int64_t j = cj; j <= j1; ++j)
-                for (int64_t i = ci; i <= i1; ++i) {
-                    const int64_t p = i + d.n0 * (j + d.n1 * k);
-                    acc += (V)a[p] * g[p * B + b];
-                }
-        out[t] = acc;
+template <typename V, int VW>
+__global__ __launch_bounds__(256) void k_model_map_t(MapDims d, const double* __restrict__ a, const V* __restrict__ g,
+                                                     V* __restrict__ out_, int B, int kc) {
+    typedef Row<V, VW> R;
+    const int64_t L = B / VW, total = d.c0 * d.c1 * L;
+    const R* __restrict__ in = (const R*)g;
+    R* __restrict__ out = (R*)out_;
+    for (int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x; t < total; t += (int64_t)gridDim.x * 256) {
+        const int64_t r = t / L, col = t - r * L, j = r / d.c0, i = r - j * d.c0;
+        const bool two_i = d.n0 > 1, two_j = d.n1 > 1;
+        const int64_t row = i + d.n0 * j;
+        auto add = [](R& x, V c, const R& y) {
+#pragma unroll
+            for (int v = 0; v < VW; ++v) x.v[v] += c * y.v[v];
+        };
+        auto nodes = [&](int64_t k, R& acc, R& own) {
+            const int64_t p = row + d.n0 * d.n1 * k;
+            const R* __restrict__ x = in + p * L + col;
+            R y[4];
+            V c[4];
+            y[0] = x[0];
+            c[0] = (V)a[p];
+            if (two_i) { y[1] = x[L]; c[1] = (V)a[p + 1]; }
+            if (two_j) {
+                y[2] = x[d.n0 * L];
+                c[2] = (V)a[p + d.n0];
+                if (two_i) { y[3] = x[(d.n0 + 1) * L]; c[3] = (V)a[p + d.n0 + 1]; }
+            }
+            own = R{};
+            add(acc, c[0], y[0]);
+            add(own, c[0], y[0]);
+            if (two_i) { add(acc, c[1], y[1]); add(own, c[1], y[1]); }
+            if (two_j) {
+                add(acc, c[2], y[2]);
+                add(own, c[2], y[2]);
+                if (two_i) { add(acc, c[3], y[3]); add(own, c[3], y[3]); }
+            }
+        };
+        for (int64_t k0 = (int64_t)blockIdx.y * kc; k0 < d.c2; k0 += (int64_t)gridDim.y * kc) {
+            const int64_t k1 = k0 + kc < d.c2 ? k0 + kc : d.c2;
+            R acc{}, own{};
+            nodes(k0, acc, own);
+            for (int64_t k = k0; k < k1; ++k) {
+                acc = own;
+                if (d.n2 > 1) nodes(k + 1, acc, own);
+                out[(i + d.c0 * (j + d.c1 * k)) * L + col] = acc;
+            }
+        }
     }
 }
 
+// (2-D: the second axis is the one walked, over rows of one node)
 static MapDims dims_of(const fm_model_map* m) {
+    if (m->dim == 2) return MapDims{m->n[0], 1, m->n[1], m->c[0], 1, m->c[1]};
     return MapDims{m->n[0], m->n[1], m->n[2], m->c[0], m->c[1], m->c[2]};
 }
 
@@ -97,8 +184,40 @@ static int check_map(const fm_model_map* m, int32_t B, int32_t precision, const 
     return FM_OK;
 }
 
-static int grid_for(int64_t work) {
-    return (int)std::min<int64_t>(std::max<int64_t>((work + 255) / 256, 1), 16384);
+// One launch of either product over `rows` rows of `planes` planes.  Columns of
+// 16 planes read one in 17 twice; shorter ones where that leaves fewer than
+// eight workgroups a CU.
+template <typename V>
+static void launch_map(void (*fn)(MapDims, const double*, const V*, V*, int, int), const fm_model_map* m, int64_t rows,
+                       int64_t planes, int B, int vw, const void* x, void* y) {
+    const int64_t bx = std::min<int64_t>((rows * (B / vw) + 255) / 256, 1 << 20);
+    int64_t kc = 16;
+    while (kc > 1 && bx * ((planes + kc - 1) / kc) < 2048) kc /= 2;
+    const int64_t by = std::min<int64_t>((planes + kc - 1) / kc, 65535);
+    hipLaunchKernelGGL(fn, dim3((unsigned)bx, (unsigned)by), dim3(256), 0, m->stream, dims_of(m), m->scale, (const V*)x, (V*)y, B,
+                       (int)kc);
+}
+
+// rows of whole 16-byte parts, on such addresses
+template <typename V>
+static bool wide(int B, const void* x, const void* y) {
+    return B % (16 / sizeof(V)) == 0 && (((uintptr_t)x | (uintptr_t)y) & 15u) == 0;
+}
+
+template <typename V>
+static void map_apply(const fm_model_map* m, int B, const void* dv, void* ds) {
+    const MapDims d = dims_of(m);
+    constexpr int vw = 16 / sizeof(V);
+    if (wide<V>(B, dv, ds)) launch_map<V>(k_model_map<V, vw>, m, d.n0 * d.n1, d.n2, B, vw, dv, ds);
+    else launch_map<V>(k_model_map<V, 1>, m, d.n0 * d.n1, d.n2, B, 1, dv, ds);
+}
+
+template <typename V>
+static void map_apply_t(const fm_model_map* m, int B, const void* g, void* out) {
+    const MapDims d = dims_of(m);
+    constexpr int vw = 16 / sizeof(V);
+    if (wide<V>(B, g, out)) launch_map<V>(k_model_map_t<V, vw>, m, d.c0 * d.c1, d.c2, B, vw, g, out);
+    else launch_map<V>(k_model_map_t<V, 1>, m, d.c0 * d.c1, d.c2, B, 1, g, out);
 }
 
 }  // namespace fm
@@ -204,13 +323,8 @@ int fm_model_map_apply(fm_model_map* m, int32_t B, int32_t precision, const void
     clear_error();
     int rc = check_map(m, B, precision, dv, ds);
     if (rc) return rc;
-    const int grid = grid_for(m->N * B);
-    if (precision == FM_FP64)
-        hipLaunchKernelGGL(k_model_map<double>, dim3(grid), dim3(256), 0, m->stream, dims_of(m), m->scale,
-                           (const double*)dv, (double*)ds, (int)B);
-    else
-        hipLaunchKernelGGL(k_model_map<float>, dim3(grid), dim3(256), 0, m->stream, dims_of(m), m->scale,
-                           (const float*)dv, (float*)ds, (int)B);
+    if (precision == FM_FP64) map_apply<double>(m, B, dv, ds);
+    else map_apply<float>(m, B, dv, ds);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("model map launch failed: %s", hipGetErrorString(e)); return FM_EHIP; }
     return FM_OK;
@@ -221,13 +335,8 @@ int fm_model_map_apply_T(fm_model_map* m, int32_t B, int32_t precision, const vo
     clear_error();
     int rc = check_map(m, B, precision, g, dv_out);
     if (rc) return rc;
-    const int grid = grid_for(m->Nc * B);
-    if (precision == FM_FP64)
-        hipLaunchKernelGGL(k_model_map_t<double>, dim3(grid), dim3(256), 0, m->stream, dims_of(m), m->scale,
-                           (const double*)g, (double*)dv_out, (int)B);
-    else
-        hipLaunchKernelGGL(k_model_map_t<float>, dim3(grid), dim3(256), 0, m->stream, dims_of(m), m->scale,
-                           (const float*)g, (float*)dv_out, (int)B);
+    if (precision == FM_FP64) map_apply_t<double>(m, B, g, dv_out);
+    else map_apply_t<float>(m, B, g, dv_out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { set_error("model map transpose launch failed: %s", hipGetErrorString(e)); return FM_EHIP; }
     return FM_OK;
