@@ -31,6 +31,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "batch.h"
 
@@ -44,9 +45,17 @@ enum : int { sAlpha = 0, sBeta, sRhobar, sPhibar, sRho, sPhi, sTheta, sInvNorm, 
 // CGLS per-column scalars, [kCgScalars][B]
 enum : int { cGamma = 0, cQQ, cAlpha, cGnew, cBeta, cRR, kCgScalars };
 
-// partial[blk][b] = sum over this block's rows of x[row][b]^2
-template <typename V>
-__global__ __launch_bounds__(kRedThreads) void k_colsq_partial(const V* __restrict__ x, int64_t rows, int B,
+// What a pass over the rows of a vector does besides adding up its squares.
+enum class Row { kRead, kSub, kAxpy };
+
+// partial[blk][b] = sum over this block's rows of y[row][b]^2, of y as it is
+// (kRead), after y = x - c y (kSub) or after y -= c x (kAxpy), c = scal[slot]:
+// the update and the norm of its result are one pass over memory.  A thread
+// keeps its column, so no element pays a division for its index.
+template <typename V, Row OP>
+__global__ __launch_bounds__(kRedThreads) void k_colsq_partial(std::conditional_t<OP == Row::kRead, const V, V>* __restrict__ y,
+                                                                const V* __restrict__ x, int64_t rows, int B,
+                                                                const double* __restrict__ scal, int slot,
                                                                 double* __restrict__ partial) {
     __shared__ double red[kRedThreads];
     const int per = kRedThreads / B;           // rows per step (B <= 256)
@@ -55,11 +64,16 @@ __global__ __launch_bounds__(kRedThreads) void k_colsq_partial(const V* __restri
     const int64_t chunk = (rows + gridDim.x - 1) / gridDim.x;
     const int64_t r0 = blockIdx.x * chunk;
     const int64_t r1 = min(rows, r0 + chunk);
+    const double c = OP == Row::kRead ? 0.0 : scal[slot * B + col];
     double acc = 0.0;
     if (lr < per)
         for (int64_t r = r0 + lr; r < r1; r += per) {
-            const double v = (double)x[r * B + col];
-            acc += v * v;
+            const int64_t t = r * B + col;
+            V v = y[t];
+            if constexpr (OP == Row::kSub) v = (V)((double)x[t] - c * (double)v);
+            if constexpr (OP == Row::kAxpy) v = (V)((double)v - c * (double)x[t]);
+            if constexpr (OP != Row::kRead) y[t] = v;
+            acc += (double)v * (double)v;
         }
     red[threadIdx.x] = (lr < per) ? acc : 0.0;
     __syncthreads();
@@ -70,65 +84,115 @@ __global__ __launch_bounds__(kRedThreads) void k_colsq_partial(const V* __restri
     }
 }
 
-// norm[b] = sqrt(sum_blk partial[blk][b]) into scalars[slot]; inverse kept too
-__global__ void k_colnorm_finalize(const double* __restrict__ partial, int nblk, int B, double* scal, int slot) {
+// The partial sums of a column added up, then the per-column scalars that
+// follow from the sum, in one launch of one workgroup.
+//   kBeta        LSQR: beta and its inverse
+//   kAlphaStart  LSQR: alpha and its inverse, phibar = beta, rhobar = alpha
+//   kAlphaRotate LSQR: alpha and its inverse, the plane rotation
+//   cStart       CGLS: gamma; the second sums are ||r||^2
+//   cStep        CGLS: ||q||^2, alpha (a zero denominator, a converged column,
+//                gives a zero step, so the column stays where it is)
+//   cDirection   CGLS: ||s||^2, beta, gamma; the second sums are ||r||^2
+// A latency chain: with one thread per column adding 512 loads in turn it took
+// 122 us (32 columns) and 39 us (one); in parallel 7 us.
+enum class Fin { kBeta, kAlphaStart, kAlphaRotate, cStart, cStep, cDirection };
+
+constexpr int kFinThreads = 1024;
+
+template <Fin OP>
+__global__ __launch_bounds__(kFinThreads) void k_colsum_finalize(const double* __restrict__ partial, int nblk, int B,
+                                                                 double* __restrict__ scal, double* __restrict__ hist,
+                                                                 int row) {
+    constexpr bool kTwo = OP == Fin::cStart || OP == Fin::cDirection;
+    __shared__ double red[kTwo ? 2 : 1][kFinThreads];
+    const int per = kFinThreads / B, col = threadIdx.x % B, lr = threadIdx.x / B;
+    for (int w = 0; w < (kTwo ? 2 : 1); ++w) {
+        double s = 0.0;
+        if (lr < per)
+            for (int q = lr; q < nblk; q += per) s += partial[((int64_t)w * nblk + q) * B + col];
+        red[w][threadIdx.x] = s;
+    }
+    int half = 1;
+    while (half < per) half *= 2;
+    for (half /= 2; half > 0; half /= 2) {
+        __syncthreads();
+        if (lr < half && lr + half < per)
+            for (int w = 0; w < (kTwo ? 2 : 1); ++w) red[w][threadIdx.x] += red[w][threadIdx.x + half * B];
+    }
     const int b = threadIdx.x;
     if (b >= B) return;
-    double s = 0.0;
-    for (int q = 0; q < nblk; ++q) s += partial[(int64_t)q * B + b];
-    const double n = sqrt(s);
-    scal[slot * B + b] = n;
-    scal[sInvNorm * B + b] = n > 0.0 ? 1.0 / n : 0.0;
+    const double sum = red[0][b];
+    if constexpr (OP == Fin::kBeta || OP == Fin::kAlphaStart || OP == Fin::kAlphaRotate) {
+        const double n = sqrt(sum);
+        scal[(OP == Fin::kBeta ? sBeta : sAlpha) * B + b] = n;
+        scal[sInvNorm * B + b] = n > 0.0 ? 1.0 / n : 0.0;
+        if constexpr (OP == Fin::kAlphaStart) {
+            scal[sPhibar * B + b] = scal[sBeta * B + b];
+            scal[sRhobar * B + b] = n;
+        }
+        if constexpr (OP == Fin::kAlphaRotate) {
+            const double alpha = n, beta = scal[sBeta * B + b];
+            const double rhobar = scal[sRhobar * B + b], phibar = scal[sPhibar * B + b];
+            const double rho = sqrt(rhobar * rhobar + beta * beta);
+            const double c = rho > 0.0 ? rhobar / rho : 0.0;
+            const double s = rho > 0.0 ? beta / rho : 0.0;
+            scal[sRho * B + b] = rho;
+            scal[sTheta * B + b] = s * alpha;
+            scal[sRhobar * B + b] = -c * alpha;
+            scal[sPhi * B + b] = c * phibar;
+            scal[sPhibar * B + b] = s * phibar;
+        }
+    } else if constexpr (OP == Fin::cStep) {
+        scal[cQQ * B + b] = sum;
+        scal[cAlpha * B + b] = sum > 0.0 ? scal[cGamma * B + b] / sum : 0.0;
+    } else {
+        if constexpr (OP == Fin::cDirection) {
+            const double g = scal[cGamma * B + b];
+            scal[cGnew * B + b] = sum;
+            scal[cBeta * B + b] = g > 0.0 ? sum / g : 0.0;
+        }
+        scal[cGamma * B + b] = sum;
+        scal[cRR * B + b] = red[1][b];
+        if (row >= 0) hist[(int64_t)row * B + b] = red[1][b];
+    }
+}
+
+// f(element, column) over the elements of a [rows][B] vector
+template <class F>
+__device__ __forceinline__ void each(int64_t rows, int B, F f) {
+    const int64_t n = rows * B, step = (int64_t)gridDim.x * blockDim.x, t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int add = (int)(step % B);
+    int b = (int)(t0 % B);
+    for (int64_t t = t0; t < n; t += step) {
+        f(t, b);
+        b += add;
+        if (b >= B) b -= B;
+    }
 }
 
 // x[:, b] *= scal[sInvNorm][b]
 template <typename V>
 __global__ void k_scale_inv(V* __restrict__ x, int64_t rows, int B, const double* __restrict__ scal) {
-    const int64_t n = rows * B;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < n; t += (int64_t)gridDim.x * blockDim.x)
-        x[t] = (V)((double)x[t] * scal[sInvNorm * B + (int)(t % B)]);
+    each(rows, B, [&](int64_t t, int b) { x[t] = (V)((double)x[t] * scal[sInvNorm * B + b]); });
 }
 
-// y[:, b] = t[:, b] - scal[slot][b] * y[:, b]
+// v = v / alpha; w = v; x = 0
 template <typename V>
-__global__ void k_sub_scaled(V* __restrict__ y, const V* __restrict__ t, int64_t rows, int B,
-                             const double* __restrict__ scal, int slot) {
-    const int64_t n = rows * B;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = (V)((double)t[i] - scal[slot * B + (int)(i % B)] * (double)y[i]);
-}
-
-// start: phibar = beta, rhobar = alpha
-__global__ void k_lsqr_start_scalars(double* scal, int B) {
-    const int b = threadIdx.x;
-    if (b >= B) return;
-    scal[sPhibar * B + b] = scal[sBeta * B + b];
-    scal[sRhobar * B + b] = scal[sAlpha * B + b];
-}
-
-// the plane rotation of one iteration, per column
-__global__ void k_lsqr_rotation(double* scal, int B) {
-    const int b = threadIdx.x;
-    if (b >= B) return;
-    const double alpha = scal[sAlpha * B + b], beta = scal[sBeta * B + b];
-    const double rhobar = scal[sRhobar * B + b], phibar = scal[sPhibar * B + b];
-    const double rho = sqrt(rhobar * rhobar + beta * beta);
-    const double c = rho > 0.0 ? rhobar / rho : 0.0;
-    const double s = rho > 0.0 ? beta / rho : 0.0;
-    scal[sRho * B + b] = rho;
-    scal[sTheta * B + b] = s * alpha;
-    scal[sRhobar * B + b] = -c * alpha;
-    scal[sPhi * B + b] = c * phibar;
-    scal[sPhibar * B + b] = s * phibar;
+__global__ void k_lsqr_first(V* __restrict__ v, V* __restrict__ x, V* __restrict__ w, int64_t rows, int B,
+                             const double* __restrict__ scal) {
+    each(rows, B, [&](int64_t t, int b) {
+        const V vn = (V)((double)v[t] * scal[sInvNorm * B + b]);
+        v[t] = vn;
+        w[t] = vn;
+        x[t] = (V)0;
+    });
 }
 
 // v = v / alpha; x += (phi/rho) w; w = v - (theta/rho) w
 template <typename V>
 __global__ void k_lsqr_xw(V* __restrict__ v, V* __restrict__ x, V* __restrict__ w, int64_t rows, int B,
                           const double* __restrict__ scal) {
-    const int64_t n = rows * B;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int b = (int)(i % B);
+    each(rows, B, [&](int64_t i, int b) {
         const double rho = scal[sRho * B + b];
         const double fphi = rho > 0.0 ? scal[sPhi * B + b] / rho : 0.0;
         const double fth = rho > 0.0 ? scal[sTheta * B + b] / rho : 0.0;
@@ -137,13 +201,7 @@ __global__ void k_lsqr_xw(V* __restrict__ v, V* __restrict__ x, V* __restrict__ 
         v[i] = (V)vn;
         x[i] = (V)((double)x[i] + fphi * wi);
         w[i] = (V)(vn - fth * wi);
-    }
-}
-
-// y = c (a fill without memset, safe inside captured graphs)
-template <typename V>
-__global__ void k_fill(V* __restrict__ y, int64_t n, V c) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) y[i] = c;
+    });
 }
 
 template <typename V>
@@ -151,54 +209,25 @@ __global__ void k_copy(V* __restrict__ y, const V* __restrict__ x, int64_t n) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) y[i] = x[i];
 }
 
-// scal[slot][b] = sum_blk partial[blk][b] (a squared column norm)
-__global__ void k_colsum_finalize(const double* __restrict__ partial, int nblk, int B, double* scal, int slot) {
-    const int b = threadIdx.x;
-    if (b >= B) return;
-    double s = 0.0;
-    for (int q = 0; q < nblk; ++q) s += partial[(int64_t)q * B + b];
-    scal[slot * B + b] = s;
-}
-
-// CGLS step length and direction scalars, per column; a zero denominator
-// (converged column) gives a zero step, so the column stays where it is
-__global__ void k_cgls_alpha(double* scal, int B) {
-    const int b = threadIdx.x;
-    if (b >= B) return;
-    const double qq = scal[cQQ * B + b];
-    scal[cAlpha * B + b] = qq > 0.0 ? scal[cGamma * B + b] / qq : 0.0;
-}
-
-__global__ void k_cgls_beta(double* scal, int B) {
-    const int b = threadIdx.x;
-    if (b >= B) return;
-    const double g = scal[cGamma * B + b], gn = scal[cGnew * B + b];
-    scal[cBeta * B + b] = g > 0.0 ? gn / g : 0.0;
-    scal[cGamma * B + b] = gn;
-}
-
-// x += alpha p (model rows) and r -= alpha q (data rows), one launch each
+// p = s; x = 0 (a fill without memset, safe inside captured graphs)
 template <typename V>
-__global__ void k_axpy_col(V* __restrict__ y, const V* __restrict__ x, int64_t rows, int B,
-                           const double* __restrict__ scal, int slot, double sign) {
-    const int64_t n = rows * B;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = (V)((double)y[i] + sign * scal[slot * B + (int)(i % B)] * (double)x[i]);
+__global__ void k_cgls_first(V* __restrict__ p, V* __restrict__ x, const V* __restrict__ s, int64_t n) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        p[i] = s[i];
+        x[i] = (V)0;
+    }
 }
 
-// hist[row][b] = scal[slot][b]
-__global__ void k_copy_row(double* __restrict__ hist, int row, const double* __restrict__ scal, int slot, int B) {
-    const int b = threadIdx.x;
-    if (b < B) hist[(int64_t)row * B + b] = scal[slot * B + b];
-}
-
-// p = s + beta p
+// x += alpha p, then p = s + beta p (x waits for the end of its iteration, so
+// that p is read once)
 template <typename V>
-__global__ void k_xpby_col(V* __restrict__ p, const V* __restrict__ s, int64_t rows, int B,
-                           const double* __restrict__ scal, int slot) {
-    const int64_t n = rows * B;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = (V)((double)s[i] + scal[slot * B + (int)(i % B)] * (double)p[i]);
+__global__ void k_cgls_xp(V* __restrict__ x, V* __restrict__ p, const V* __restrict__ s, int64_t rows, int B,
+                          const double* __restrict__ scal) {
+    each(rows, B, [&](int64_t i, int b) {
+        const double pi = (double)p[i];
+        x[i] = (V)((double)x[i] + scal[cAlpha * B + b] * pi);
+        p[i] = (V)((double)s[i] + scal[cBeta * B + b] * pi);
+    });
 }
 
 }  // namespace fm
@@ -239,13 +268,22 @@ namespace fm {
 static int grid_for(int64_t n) { return (int)std::min<int64_t>((n + 255) / 256, 8192); }
 
 template <typename V>
-static int colnorm(fm_lsqr* L, const void* x, int64_t rows, int slot) {
-    fm_batch* b = L->b;
-    hipLaunchKernelGGL(k_colsq_partial<V>, dim3(kRedBlocks), dim3(kRedThreads), 0, b->stream, (const V*)x, rows,
-                       b->B, L->partial);
-    hipLaunchKernelGGL(k_colnorm_finalize, dim3(1), dim3(std::max(64, b->B)), 0, b->stream,
-                       (const double*)L->partial, kRedBlocks, b->B, L->scal, slot);
-    return hipGetLastError() == hipSuccess ? FM_OK : FM_EHIP;
+static void colsq(const fm_batch* b, double* partial, const void* y, int64_t rows) {
+    hipLaunchKernelGGL((k_colsq_partial<V, Row::kRead>), dim3(kRedBlocks), dim3(kRedThreads), 0, b->stream, (const V*)y,
+                       (const V*)nullptr, rows, b->B, (const double*)nullptr, 0, partial);
+}
+
+// y = x - c y or y -= c x, and the partial sums of its squares
+template <typename V, Row OP>
+static void update_sq(const fm_batch* b, double* partial, void* y, const void* x, int64_t rows, const double* scal, int slot) {
+    hipLaunchKernelGGL((k_colsq_partial<V, OP>), dim3(kRedBlocks), dim3(kRedThreads), 0, b->stream, (V*)y, (const V*)x,
+                       rows, b->B, scal, slot, partial);
+}
+
+template <Fin OP>
+static void finalize(const fm_batch* b, const double* partial, double* scal, double* hist = nullptr, int row = -1) {
+    hipLaunchKernelGGL(k_colsum_finalize<OP>, dim3(1), dim3(kFinThreads), 0, b->stream, partial, kRedBlocks, b->B, scal,
+                       hist, row);
 }
 
 template <typename V>
@@ -253,19 +291,16 @@ static int lsqr_start(fm_lsqr* L, const void* d) {
     fm_batch* b = L->b;
     const int64_t nd = (int64_t)b->S * b->R, nm = b->N;
     hipLaunchKernelGGL(k_copy<V>, dim3(grid_for(nd * b->B)), dim3(256), 0, b->stream, (V*)L->u, (const V*)d, nd * b->B);
-    int rc = colnorm<V>(L, L->u, nd, sBeta);
-    if (rc) return rc;
+    colsq<V>(b, L->partial, L->u, nd);
+    finalize<Fin::kBeta>(b, L->partial, L->scal);
     hipLaunchKernelGGL(k_scale_inv<V>, dim3(grid_for(nd * b->B)), dim3(256), 0, b->stream, (V*)L->u, nd, b->B,
                        (const double*)L->scal);
-    rc = apply_JT(b, L->u, FM_W_RECEIVERS, L->v, FM_JT_SUMMED);
+    int rc = apply_JT(b, L->u, FM_W_RECEIVERS, L->v, FM_JT_SUMMED);
     if (rc) return rc;
-    rc = colnorm<V>(L, L->v, nm, sAlpha);
-    if (rc) return rc;
-    hipLaunchKernelGGL(k_scale_inv<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)L->v, nm, b->B,
-                       (const double*)L->scal);
-    hipLaunchKernelGGL(k_copy<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)L->w, (const V*)L->v, nm * b->B);
-    hipLaunchKernelGGL(k_fill<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)L->x, nm * b->B, (V)0);
-    hipLaunchKernelGGL(k_lsqr_start_scalars, dim3(1), dim3(std::max(64, b->B)), 0, b->stream, L->scal, b->B);
+    colsq<V>(b, L->partial, L->v, nm);
+    finalize<Fin::kAlphaStart>(b, L->partial, L->scal);
+    hipLaunchKernelGGL(k_lsqr_first<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)L->v, (V*)L->x, (V*)L->w,
+                       nm, b->B, (const double*)L->scal);
     return hipGetLastError() == hipSuccess ? FM_OK : FM_EHIP;
 }
 
@@ -276,19 +311,14 @@ static int lsqr_iterate(fm_lsqr* L, int n) {
     for (int it = 0; it < n; ++it) {
         int rc = apply_J(b, L->v, FM_DS_BROADCAST, L->td, FM_OUT_RECEIVERS);
         if (rc) return rc;
-        hipLaunchKernelGGL(k_sub_scaled<V>, dim3(grid_for(nd * b->B)), dim3(256), 0, b->stream, (V*)L->u,
-                           (const V*)L->td, nd, b->B, (const double*)L->scal, (int)sAlpha);
-        rc = colnorm<V>(L, L->u, nd, sBeta);
-        if (rc) return rc;
+        update_sq<V, Row::kSub>(b, L->partial, L->u, L->td, nd, L->scal, sAlpha);
+        finalize<Fin::kBeta>(b, L->partial, L->scal);
         hipLaunchKernelGGL(k_scale_inv<V>, dim3(grid_for(nd * b->B)), dim3(256), 0, b->stream, (V*)L->u, nd, b->B,
                            (const double*)L->scal);
         rc = apply_JT(b, L->u, FM_W_RECEIVERS, L->tv, FM_JT_SUMMED);
         if (rc) return rc;
-        hipLaunchKernelGGL(k_sub_scaled<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)L->v,
-                           (const V*)L->tv, nm, b->B, (const double*)L->scal, (int)sBeta);
-        rc = colnorm<V>(L, L->v, nm, sAlpha);
-        if (rc) return rc;
-        hipLaunchKernelGGL(k_lsqr_rotation, dim3(1), dim3(std::max(64, b->B)), 0, b->stream, L->scal, b->B);
+        update_sq<V, Row::kSub>(b, L->partial, L->v, L->tv, nm, L->scal, sBeta);
+        finalize<Fin::kAlphaRotate>(b, L->partial, L->scal);
         hipLaunchKernelGGL(k_lsqr_xw<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)L->v, (V*)L->x,
                            (V*)L->w, nm, b->B, (const double*)L->scal);
         if (hipGetLastError() != hipSuccess) { set_error("LSQR kernel launch failed"); return FM_EHIP; }
@@ -383,28 +413,21 @@ void lsqr_free(fm_lsqr* L) { lsqr_release(L); }
 // ---------------------------------------------------------------------------
 // CGLS
 // ---------------------------------------------------------------------------
-template <typename V>
-static void colsq(fm_batch* b, double* partial, double* scal, const void* x, int64_t rows, int slot) {
-    hipLaunchKernelGGL(k_colsq_partial<V>, dim3(kRedBlocks), dim3(kRedThreads), 0, b->stream, (const V*)x, rows,
-                       b->B, partial);
-    hipLaunchKernelGGL(k_colsum_finalize, dim3(1), dim3(std::max(64, b->B)), 0, b->stream, (const double*)partial,
-                       kRedBlocks, b->B, scal, slot);
-}
-
+// (the second half of the partial sums is the residual's)
 template <typename V>
 static int cgls_start(fm_cgls* C, const void* d) {
     fm_batch* b = C->b;
     const int64_t nd = (int64_t)b->S * b->R, nm = b->N;
+    double* const partial_r = C->partial + (size_t)kRedBlocks * b->B;
     hipLaunchKernelGGL(k_copy<V>, dim3(grid_for(nd * b->B)), dim3(256), 0, b->stream, (V*)C->r, (const V*)d, nd * b->B);
     int rc = apply_JT(b, C->r, FM_W_RECEIVERS, C->s, FM_JT_SUMMED);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_copy<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)C->p, (const V*)C->s, nm * b->B);
-    hipLaunchKernelGGL(k_fill<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)C->x, nm * b->B, (V)0);
-    colsq<V>(b, C->partial, C->scal, C->s, nm, cGamma);
-    colsq<V>(b, C->partial, C->scal, C->r, nd, cRR);
+    hipLaunchKernelGGL(k_cgls_first<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)C->p, (V*)C->x,
+                       (const V*)C->s, nm * b->B);
+    colsq<V>(b, C->partial, C->s, nm);
+    colsq<V>(b, partial_r, C->r, nd);
     C->it = 0;
-    hipLaunchKernelGGL(k_copy_row, dim3(1), dim3(std::max(64, b->B)), 0, b->stream, C->hist, 0,
-                       (const double*)C->scal, (int)cRR, b->B);
+    finalize<Fin::cStart>(b, C->partial, C->scal, C->hist, 0);
     if (hipGetLastError() != hipSuccess) { set_error("CGLS kernel launch failed"); return FM_EHIP; }
     return FM_OK;
 }
@@ -413,25 +436,20 @@ template <typename V>
 static int cgls_iterate(fm_cgls* C, int n) {
     fm_batch* b = C->b;
     const int64_t nd = (int64_t)b->S * b->R, nm = b->N;
+    double* const partial_r = C->partial + (size_t)kRedBlocks * b->B;
     for (int it = 0; it < n; ++it) {
         int rc = apply_J(b, C->p, FM_DS_BROADCAST, C->q, FM_OUT_RECEIVERS);
         if (rc) return rc;
-        colsq<V>(b, C->partial, C->scal, C->q, nd, cQQ);
-        hipLaunchKernelGGL(k_cgls_alpha, dim3(1), dim3(std::max(64, b->B)), 0, b->stream, C->scal, b->B);
-        hipLaunchKernelGGL(k_axpy_col<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)C->x,
-                           (const V*)C->p, nm, b->B, (const double*)C->scal, (int)cAlpha, 1.0);
-        hipLaunchKernelGGL(k_axpy_col<V>, dim3(grid_for(nd * b->B)), dim3(256), 0, b->stream, (V*)C->r,
-                           (const V*)C->q, nd, b->B, (const double*)C->scal, (int)cAlpha, -1.0);
+        colsq<V>(b, C->partial, C->q, nd);
+        finalize<Fin::cStep>(b, C->partial, C->scal);
+        update_sq<V, Row::kAxpy>(b, partial_r, C->r, C->q, nd, C->scal, cAlpha);
         rc = apply_JT(b, C->r, FM_W_RECEIVERS, C->s, FM_JT_SUMMED);
         if (rc) return rc;
-        colsq<V>(b, C->partial, C->scal, C->s, nm, cGnew);
-        hipLaunchKernelGGL(k_cgls_beta, dim3(1), dim3(std::max(64, b->B)), 0, b->stream, C->scal, b->B);
-        hipLaunchKernelGGL(k_xpby_col<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)C->p,
-                           (const V*)C->s, nm, b->B, (const double*)C->scal, (int)cBeta);
-        colsq<V>(b, C->partial, C->scal, C->r, nd, cRR);
-        if (++C->it <= C->max_iter)
-            hipLaunchKernelGGL(k_copy_row, dim3(1), dim3(std::max(64, b->B)), 0, b->stream, C->hist, C->it,
-                               (const double*)C->scal, (int)cRR, b->B);
+        colsq<V>(b, C->partial, C->s, nm);
+        ++C->it;
+        finalize<Fin::cDirection>(b, C->partial, C->scal, C->hist, C->it <= C->max_iter ? C->it : -1);
+        hipLaunchKernelGGL(k_cgls_xp<V>, dim3(grid_for(nm * b->B)), dim3(256), 0, b->stream, (V*)C->x, (V*)C->p,
+                           (const V*)C->s, nm, b->B, (const double*)C->scal);
         if (hipGetLastError() != hipSuccess) { set_error("CGLS kernel launch failed"); return FM_EHIP; }
     }
     return FM_OK;
@@ -463,7 +481,7 @@ int cgls_create(fm_batch* b, int32_t max_iter, fm_cgls** out) {
     size_t sizes[] = {nm, nm, nm, nd, nd};
     for (int i = 0; i < 5 && e == hipSuccess; i++) e = hipMalloc(targets[i], sizes[i]);
     if (e == hipSuccess) e = hipMalloc((void**)&C->scal, sizeof(double) * kCgScalars * b->B);
-    if (e == hipSuccess) e = hipMalloc((void**)&C->partial, sizeof(double) * kRedBlocks * b->B);
+    if (e == hipSuccess) e = hipMalloc((void**)&C->partial, sizeof(double) * 2 * kRedBlocks * b->B);
     if (e == hipSuccess) e = hipMalloc((void**)&C->hist, sizeof(double) * ((size_t)max_iter + 1) * b->B);
     if (e != hipSuccess) {
         cgls_release(C);
