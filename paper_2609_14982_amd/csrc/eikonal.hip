@@ -32,6 +32,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <utility>
 #include <vector>
 
 #include "fmbtf.h"
@@ -45,6 +46,7 @@ struct fm_eikonal {
     int32_t S = 0;                  // capacity in sources
     double* X = nullptr;            // device [N][dim]
     double* Tb = nullptr;           // device [S][N] second buffer
+    void* block = nullptr;          // holds the device arrays below
     int64_t W = 0;                  // words of 64 nodes per source (a multiple of kTile)
     uint16_t* list = nullptr;       // device [S][W / 64][4096] nodes of a tile to recompute
     int32_t* count = nullptr;       // device [S][W / 64] their number
@@ -419,19 +421,30 @@ int fm_eikonal_create(int32_t dim, int64_t n1, int64_t n2, int64_t n3, const dou
     if (h == hipSuccess) h = hipMalloc(&e->X, sizeof(double) * (size_t)N * dim);
     if (h == hipSuccess) h = hipMalloc(&e->Tb, sizeof(double) * nsn);
     e->W = (N + 64 * kTile - 1) / (64 * kTile) * kTile;
-    const size_t words = sizeof(uint64_t) * (size_t)max_sources * (size_t)e->W;
-    if (h == hipSuccess) h = hipMalloc(&e->chg[0], words);
-    if (h == hipSuccess) h = hipMalloc(&e->chg[1], words);
-    if (h == hipSuccess) h = hipMalloc(&e->seed, words);
-    if (h == hipSuccess) h = hipMalloc(&e->edge, sizeof(uint64_t) * 4 * (size_t)e->W);
-    if (h == hipSuccess) h = hipMalloc(&e->list, sizeof(uint16_t) * 64 * (size_t)max_sources * (size_t)e->W);
-    if (h == hipSuccess) h = hipMalloc(&e->count, sizeof(int32_t) * (size_t)max_sources * (size_t)(e->W / kTile));
-    if (h == hipSuccess) h = hipMalloc(&e->batch, sizeof(uint32_t) * (size_t)max_sources * (size_t)e->W);
+    // one allocation for the small arrays (0.2 ms each otherwise), 256-byte parts
+    const size_t src = (size_t)max_sources, W = (size_t)e->W;
+    const std::pair<void**, size_t> parts[] = {{(void**)&e->chg[0], sizeof(uint64_t) * src * W},
+                                               {(void**)&e->chg[1], sizeof(uint64_t) * src * W},
+                                               {(void**)&e->seed, sizeof(uint64_t) * src * W},
+                                               {(void**)&e->edge, sizeof(uint64_t) * 4 * W},
+                                               {(void**)&e->list, sizeof(uint16_t) * 64 * src * W},
+                                               {(void**)&e->count, sizeof(int32_t) * src * (W / kTile)},
+                                               {(void**)&e->batch, sizeof(uint32_t) * src * W},
+                                               {(void**)&e->xi, sizeof(double) * 3 * src},
+                                               {(void**)&e->n_batch, sizeof(unsigned) * (kChunk + 1)}};
+    size_t all = 0;
+    for (const auto& x : parts) all += (x.second + 255) & ~size_t(255);
+    if (h == hipSuccess) h = hipMalloc(&e->block, all);
+    if (h == hipSuccess) {
+        char* at = (char*)e->block;
+        for (const auto& x : parts) {
+            *x.first = at;
+            at += (x.second + 255) & ~size_t(255);
+        }
+    }
     int cus = 0;
     if (h == hipSuccess) h = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, e->device);
     e->waves = cus * 24;    // 12 a CU are resident; more for the batches' different lengths
-    if (h == hipSuccess) h = hipMalloc(&e->xi, sizeof(double) * 3 * (size_t)max_sources);
-    if (h == hipSuccess) h = hipMalloc(&e->n_batch, sizeof(unsigned) * (kChunk + 1));
     if (h == hipSuccess) h = hipHostMalloc((void**)&e->n_batch_h, sizeof(unsigned) * (kChunk + 1), hipHostMallocDefault);
     if (h == hipSuccess) h = hipMemcpy(e->X, X, sizeof(double) * (size_t)N * dim, hipMemcpyHostToDevice);
     if (h == hipSuccess) {
@@ -541,15 +554,7 @@ void fm_eikonal_free(fm_eikonal* e) {
     if (!e) return;
     if (e->X) (void)hipFree(e->X);
     if (e->Tb) (void)hipFree(e->Tb);
-    if (e->chg[0]) (void)hipFree(e->chg[0]);
-    if (e->chg[1]) (void)hipFree(e->chg[1]);
-    if (e->seed) (void)hipFree(e->seed);
-    if (e->edge) (void)hipFree(e->edge);
-    if (e->list) (void)hipFree(e->list);
-    if (e->count) (void)hipFree(e->count);
-    if (e->batch) (void)hipFree(e->batch);
-    if (e->xi) (void)hipFree(e->xi);
-    if (e->n_batch) (void)hipFree(e->n_batch);
+    if (e->block) (void)hipFree(e->block);
     if (e->n_batch_h) (void)hipHostFree(e->n_batch_h);
     delete e;
 }

@@ -23,6 +23,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <condition_variable>
 #include <mutex>
@@ -358,9 +359,13 @@ __global__ void k_trim_flags(int64_t total, const int32_t* __restrict__ lf, cons
 
 // The host threads' level eliminations, batched: each thread hands over
 // the arguments of its two eliminations (inputs already on the device) and
-// waits; the server launches every job pending at that moment in one launch
-// per direction, so that the small one-workgroup eliminations of many
-// sources run side by side instead of queueing behind each other.
+// waits; a server thread launches every job pending at that moment in one
+// launch for both directions, so that the small one-workgroup eliminations of
+// many sources run side by side instead of queueing behind each other.  A
+// launch takes 14 ns a node (7 ms on 101x101x51) whatever the number of jobs, so
+// the first job waits a seventh of that for the others, and jobs that come
+// later start beside it from a second thread (three launches in turn took
+// 22 ms for 8 sources; a launch for each job, from four threads, 29 ms).
 struct LevelServer {
     struct Job {
         KahnArgs f, r;
@@ -372,7 +377,10 @@ struct LevelServer {
     std::vector<Job*> pending;
     bool stop = false;
     int device = 0;
-    std::thread th;
+    size_t most = 1;             // jobs that can be pending at once
+    std::chrono::nanoseconds gather{0};
+    static constexpr int kThreads = 2;
+    std::vector<std::thread> th;
     void run() {
         hipStream_t st = nullptr;
         KahnArgs* dargs = nullptr;
@@ -385,6 +393,8 @@ struct LevelServer {
                 std::unique_lock<std::mutex> lk(mu);
                 cv_job.wait(lk, [&]() { return stop || !pending.empty(); });
                 if (pending.empty()) break;
+                cv_job.wait_for(lk, gather, [&]() { return stop || pending.empty() || pending.size() >= most; });
+                if (pending.empty()) continue;      // the other thread took them
                 batch.swap(pending);
             }
             const size_t n = batch.size();
@@ -421,13 +431,15 @@ struct LevelServer {
     hipError_t submit(Job& j) {
         std::unique_lock<std::mutex> lk(mu);
         pending.push_back(&j);
-        cv_job.notify_one();
+        cv_job.notify_all();
         cv_done.wait(lk, [&]() { return j.done; });
         return j.err;
     }
-    void start(int dev) {
+    void start(int dev, size_t jobs, int64_t nodes) {
         device = dev;
-        th = std::thread([this]() { run(); });
+        most = jobs;
+        gather = std::chrono::nanoseconds(2 * nodes);
+        for (int i = 0; i < kThreads; i++) th.emplace_back([this]() { run(); });
     }
     void finish() {
         {
@@ -435,9 +447,34 @@ struct LevelServer {
             stop = true;
         }
         cv_job.notify_all();
-        if (th.joinable()) th.join();
+        for (std::thread& t : th) t.join();
     }
 };
+
+// One device allocation for several arrays.  hipMalloc and hipFree take 0.2 ms
+// each and one at a time whichever thread calls them: with an allocation per
+// array, 8 sources on 101x101x51 spent 54 ms of a 165 ms pass (setup, batch, one
+// J^T) in 215 hipFree calls alone.
+struct Part {
+    void** p;
+    size_t bytes;
+};
+
+hipError_t carve(void** block, const std::vector<Part>& parts) {
+    size_t total = 0;
+    for (const Part& x : parts) total += (x.bytes + 255) & ~size_t(255);
+    const hipError_t e = hipMalloc(block, std::max<size_t>(total, 256));
+    if (e != hipSuccess) {
+        *block = nullptr;
+        return e;
+    }
+    char* at = (char*)*block;
+    for (const Part& x : parts) {
+        *x.p = at;
+        at += (x.bytes + 255) & ~size_t(255);
+    }
+    return hipSuccess;
+}
 
 // Per host thread: a stream, device buffers and pinned host staging for the
 // condensation levels and the records of the states it finishes.
@@ -461,12 +498,24 @@ struct LevelCtx {
     // pass (not owned)
     const double *src_w6 = nullptr, *src_cal = nullptr;
     const uint8_t* src_pm = nullptr;
+    void* block = nullptr;       // holds every array above but w6 and cal
+    // the arrays for components numbered below c on a grid of N nodes
+    hipError_t reserve(int64_t c, int64_t N) {
+        const size_t n = (size_t)N, k = (size_t)c, i = sizeof(int32_t);
+        const hipError_t e = carve(&block, {{(void**)&cid, i * k}, {(void**)&bmem, i * k}, {(void**)&cnt, i * k},
+                                            {(void**)&f0, i * k}, {(void**)&f1, i * k}, {(void**)&lf, i * k},
+                                            {(void**)&lr, i * k}, {(void**)&cnt_r, i * k}, {(void**)&f0_r, i * k},
+                                            {(void**)&f1_r, i * k}, {(void**)&bptr, i * (k + 1)}, {(void**)&pm, n},
+                                            {(void**)&sm, n}, {(void**)&pos, i * n}, {(void**)&comp, i * n},
+                                            {(void**)&bsum, i * ((n + 1023) / 1024 + 1)}, {(void**)&rcv, n},
+                                            {(void**)&extm, n}});
+        if (e == hipSuccess) cap = c;
+        return e;
+    }
     void release() {
-        for (void* p : {(void*)cid, (void*)bptr, (void*)bmem, (void*)cnt, (void*)f0, (void*)f1, (void*)lf, (void*)lr,
-                        (void*)cnt_r, (void*)f0_r, (void*)f1_r,
-                        (void*)pm, (void*)sm, (void*)pos, (void*)comp, (void*)bsum, (void*)w6, (void*)cal, (void*)rcv,
-                        (void*)extm})
+        for (void* p : {block, (void*)w6, (void*)cal})
             if (p) (void)hipFree(p);
+        block = nullptr;
         if (host) (void)hipHostFree(host);
         if (stream) (void)hipStreamDestroy(stream);
         cid = bptr = bmem = cnt = f0 = f1 = lf = lr = nullptr;
@@ -588,18 +637,9 @@ int device_pack(void* ctxp, bool fwd, int64_t N, const int32_t* pos_of, const in
     hipError_t e = hipSuccess;
     if (!x.stream) e = hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking);
     const int64_t nb = (N + 1023) / 1024;
-    if (e == hipSuccess && !x.pos) {
-        e = hipMalloc(&x.pos, sizeof(int32_t) * (size_t)N);
-        if (e == hipSuccess) e = hipMalloc(&x.comp, sizeof(int32_t) * (size_t)N);
-        if (e == hipSuccess) e = hipMalloc(&x.bsum, sizeof(int32_t) * (size_t)(nb + 1));
-        if (e == hipSuccess && !x.src_w6) e = hipMalloc(&x.w6, sizeof(double) * 6 * (size_t)N);
-        if (e == hipSuccess && !x.src_cal) e = hipMalloc(&x.cal, sizeof(double) * (size_t)N);
-        if (e == hipSuccess) e = hipMalloc(&x.rcv, (size_t)N);
-        if (e == hipSuccess) e = hipMalloc(&x.extm, (size_t)N);
-        if (e == hipSuccess && !x.pm) e = hipMalloc(&x.pm, (size_t)N);
-        if (e == hipSuccess && !x.sm) e = hipMalloc(&x.sm, (size_t)N);
-        if (e == hipSuccess && !x.cnt) e = hipMalloc(&x.cnt, sizeof(int32_t) * (size_t)N);
-    }
+    if (e == hipSuccess && !x.block) e = x.reserve(N, N);
+    if (e == hipSuccess && !x.src_w6 && !x.w6) e = hipMalloc(&x.w6, sizeof(double) * 6 * (size_t)N);
+    if (e == hipSuccess && !x.src_cal && !x.cal) e = hipMalloc(&x.cal, sizeof(double) * (size_t)N);
     hipStream_t s = x.stream;
     const int d = fwd ? 0 : 1;
     std::vector<uint8_t> m8;
@@ -678,17 +718,11 @@ int device_levels(void* ctxp, int64_t N, int32_t ncomp, const int32_t* comp, con
         }
     const int64_t need = N + nblk;
     hipError_t e = hipSuccess;
-    if (!x.stream) e = hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking);
-    if (e == hipSuccess && x.cap < need) {
+    if (x.cap < need || !x.host) {
         const int64_t cap = std::max<int64_t>(need, N + N / 64 + 64);
         x.release();
         e = hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking);
-        x.cap = cap;
-        for (int32_t** p : {&x.cid, &x.bmem, &x.cnt, &x.f0, &x.f1, &x.lf, &x.lr, &x.cnt_r, &x.f0_r, &x.f1_r})
-            if (e == hipSuccess) e = hipMalloc(p, sizeof(int32_t) * (size_t)cap);
-        if (e == hipSuccess) e = hipMalloc(&x.bptr, sizeof(int32_t) * ((size_t)cap + 1));
-        if (e == hipSuccess) e = hipMalloc(&x.pm, (size_t)N);
-        if (e == hipSuccess) e = hipMalloc(&x.sm, (size_t)N);
+        if (e == hipSuccess) e = x.reserve(cap, N);
         if (e == hipSuccess) e = hipHostMalloc((void**)&x.host, sizeof(int32_t) * (size_t)(4 * cap + 2) + 2 * (size_t)N);
     }
     if (e != hipSuccess) {
@@ -844,6 +878,7 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
     uint8_t *dm = nullptr, *dsm = nullptr, *dtr = nullptr;
     int32_t *dcnt = nullptr, *df0 = nullptr, *df1 = nullptr, *dlf = nullptr, *dlr = nullptr;
     int32_t *dcnt_r = nullptr, *df0_r = nullptr, *df1_r = nullptr;
+    void* block = nullptr;       // holds all of these
     int64_t* dsrc = nullptr;
     unsigned long long* dnv = nullptr;
     int* dbad = nullptr;
@@ -856,28 +891,27 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
         x.server = &server;
     }
     auto release = [&]() {
-        for (void* p : {(void*)dG, (void*)ds, (void*)dw, (void*)dc, (void*)dm, (void*)dsrc, (void*)dnv, (void*)dbad,
-                        (void*)dsm, (void*)dtr, (void*)dcnt, (void*)df0, (void*)df1, (void*)dlf, (void*)dlr,
-                        (void*)dcnt_r, (void*)df0_r, (void*)df1_r})
-            if (p) (void)hipFree(p);
+        if (block) (void)hipFree(block);
         for (LevelCtx& x : lctx) x.release();
         if (hst) (void)hipHostFree(hst);
     };
     hipError_t e = hipGetDevice(&dev);
     for (LevelCtx& x : lctx) x.device = dev;
-    if (e == hipSuccess) e = hipMalloc(&dG, sizeof(double) * (size_t)N * d.ncomp_g);
-    if (e == hipSuccess) e = hipMalloc(&ds, sizeof(double) * (size_t)N);
-    if (e == hipSuccess) e = hipMalloc(&dw, sizeof(double) * 6 * (size_t)N * chunk);
-    if (e == hipSuccess) e = hipMalloc(&dc, sizeof(double) * (size_t)N * chunk);
-    if (e == hipSuccess) e = hipMalloc(&dm, (size_t)N * chunk);
-    if (e == hipSuccess) e = hipMalloc(&dsm, (size_t)N * chunk);
-    if (e == hipSuccess) e = hipMalloc(&dtr, (size_t)N * chunk);
+    const size_t nc = (size_t)N * chunk;
+    std::vector<Part> parts = {{(void**)&dG, sizeof(double) * (size_t)N * d.ncomp_g},
+                               {(void**)&ds, sizeof(double) * (size_t)N},
+                               {(void**)&dw, sizeof(double) * 6 * nc},
+                               {(void**)&dc, sizeof(double) * nc},
+                               {(void**)&dm, nc},
+                               {(void**)&dsm, nc},
+                               {(void**)&dtr, nc},
+                               {(void**)&dsrc, sizeof(int64_t) * S},
+                               {(void**)&dnv, sizeof(unsigned long long) * S},
+                               {(void**)&dbad, sizeof(int) * S}};
     for (int32_t** p : {&dcnt, &df0, &df1, &dlf, &dlr, &dcnt_r, &df0_r, &df1_r})
-        if (e == hipSuccess) e = hipMalloc(p, sizeof(int32_t) * (size_t)N * chunk);
+        parts.push_back({(void**)p, sizeof(int32_t) * nc});
+    if (e == hipSuccess) e = carve(&block, parts);
     if (e == hipSuccess) e = hipHostMalloc((void**)&hst, (size_t)N * chunk * (2 + 7 * sizeof(double)));
-    if (e == hipSuccess) e = hipMalloc(&dsrc, sizeof(int64_t) * S);
-    if (e == hipSuccess) e = hipMalloc(&dnv, sizeof(unsigned long long) * S);
-    if (e == hipSuccess) e = hipMalloc(&dbad, sizeof(int) * S);
     if (e == hipSuccess) e = hipMemcpy(dG, g->G, sizeof(double) * (size_t)N * d.ncomp_g, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(ds, s, sizeof(double) * (size_t)N, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(dsrc, src_nodes, sizeof(int64_t) * S, hipMemcpyHostToDevice);
@@ -891,6 +925,9 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
     struct Couplings {
         std::vector<uint8_t> m, t;
         std::vector<double> w, c;
+        // the same in these vectors or, for the last chunk, in the staging
+        const uint8_t *pm = nullptr, *pt = nullptr;
+        const double *pw = nullptr, *pc = nullptr;
         void* dev = nullptr;     // device copy of w [N][6], c [N], m [N] for the host thread's device work
     };
     std::vector<Couplings> buf(S);
@@ -922,8 +959,8 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
                 if (next.load() >= S || (stop && next.load() >= ready)) return;
                 a = next.fetch_add(1);
             }
-            Assembled pre{buf[a].m.data(), buf[a].w.data(), buf[a].c.data(), (int64_t)nv[a]};
-            pre.trim = buf[a].t.data();
+            Assembled pre{buf[a].pm, buf[a].pw, buf[a].pc, (int64_t)nv[a]};
+            pre.trim = buf[a].pt;
             pre.levels = device_levels;
             pre.pack = device_pack;
             pre.ctx = &lctx[id];
@@ -957,7 +994,7 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
             std::vector<double>().swap(buf[a].c);
         }
     };
-    server.start(dev);
+    server.start(dev, (size_t)std::min<int32_t>(nt, S), N);
     std::vector<std::thread> th;
     for (int i = 0; i < nt; i++) th.emplace_back(worker, i);
     int rc = FM_OK;
@@ -1013,6 +1050,17 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
         // each source's couplings stay on the device for its host thread
         // (their device work then needs no upload); without the memory for
         // it the host thread uploads them
+        const size_t copy = ((size_t)N * (6 * sizeof(double) + sizeof(double) + 1) + 255) & ~size_t(255);
+        if (a0 == 0) {
+            void* p = nullptr;
+            if (hipMalloc(&p, copy * (size_t)n) == hipSuccess) {
+                std::lock_guard<std::mutex> lk(pool_mu);
+                pool_all.push_back(p);
+                for (int32_t k = 0; k < n; k++) pool_free.push_back((char*)p + copy * (size_t)k);
+            } else {
+                (void)hipGetLastError();
+            }
+        }
         for (int32_t k = 0; k < n && e == hipSuccess; k++) {
             void* p = nullptr;
             {
@@ -1023,7 +1071,7 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
                 }
             }
             if (!p) {
-                if (hipMalloc(&p, (size_t)N * (6 * sizeof(double) + sizeof(double) + 1)) != hipSuccess) {
+                if (hipMalloc(&p, copy) != hipSuccess) {
                     (void)hipGetLastError();
                     break;
                 }
@@ -1040,18 +1088,34 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
         }
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         // the next chunk's device work runs while this one is copied out of
-        // the staging (one host thread per source)
-        if (e == hipSuccess && a0 + chunk < S) e = launch_chunk(a0 + chunk);
-        {
+        // the staging (one host thread per source); nothing overwrites the last
+        // chunk's, which is read where it is (24 ms for 8 sources on 101x101x51)
+        const bool last = a0 + chunk >= S;
+        if (e == hipSuccess && !last) e = launch_chunk(a0 + chunk);
+        auto hand_over = [&](int32_t k) {
+            Couplings& cp = buf[a0 + k];
+            const uint8_t *pm = hm + (size_t)k * N, *pt = ht + (size_t)k * N;
+            const double *pw = hw + (size_t)k * N * 6, *pc = hc + (size_t)k * N;
+            if (!last) {
+                cp.m.assign(pm, pm + N);
+                cp.t.assign(pt, pt + N);
+                cp.w.assign(pw, pw + (size_t)N * 6);
+                cp.c.assign(pc, pc + N);
+                pm = cp.m.data();
+                pt = cp.t.data();
+                pw = cp.w.data();
+                pc = cp.c.data();
+            }
+            cp.pm = pm;
+            cp.pt = pt;
+            cp.pw = pw;
+            cp.pc = pc;
+        };
+        if (last) {
+            for (int32_t k = 0; k < n; k++) hand_over(k);
+        } else {
             std::vector<std::thread> cps;
-            for (int32_t k = 0; k < n; k++)
-                cps.emplace_back([&, k]() {
-                    Couplings& cp = buf[a0 + k];
-                    cp.m.assign(hm + (size_t)k * N, hm + (size_t)(k + 1) * N);
-                    cp.t.assign(ht + (size_t)k * N, ht + (size_t)(k + 1) * N);
-                    cp.w.assign(hw + (size_t)k * N * 6, hw + (size_t)(k + 1) * N * 6);
-                    cp.c.assign(hc + (size_t)k * N, hc + (size_t)(k + 1) * N);
-                });
+            for (int32_t k = 0; k < n; k++) cps.emplace_back(hand_over, k);
             for (auto& t : cps) t.join();
         }
         for (int32_t k = 0; k < n && rc == FM_OK; k++)
