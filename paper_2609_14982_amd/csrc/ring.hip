@@ -613,39 +613,47 @@ __global__ __launch_bounds__((CW + OW + FW) * 64) void k_ring(ApplyArgs a, RingA
 // inputs in level order
 // ---------------------------------------------------------------------------
 
-constexpr int kPermRows = 64;
-constexpr int kPermCols = 32;
+constexpr int kPermRows = 256;
 
-// q[alpha][g][p][r] = c ds (forward) or w (transpose) of the node at position
-// p: rows read whole, transposed in LDS, written as one stream per group.
-template <int DIR, typename V>
-__global__ __launch_bounds__(256) void k_ring_q(ApplyArgs a, RingArgs r, V* __restrict__ q) {
-    __shared__ V tile[kPermCols][kPermRows + 1];
-    const int alpha = blockIdx.y;
-    if (blockIdx.x == 0 && threadIdx.x == 0 && r.xmask) r.xmask[(size_t)alpha * 32] = 0u;
+// q[alpha][b][p] = c ds (forward) or w (transpose) of the node at position p:
+// CL columns of 256 rows at a time, rows read by CL lanes, transposed in LDS,
+// written 256 values at a time.  Bound by the rows in flight: a lane has CL
+// loads outstanding (with four of 64-row tiles the pass took 300 us for 8 x 16
+// on 101x101x51, 1.07 GB).
+template <int DIR, typename V, int CL>
+__global__ __launch_bounds__(kPermRows) void k_ring_q(ApplyArgs a, RingArgs r, V* __restrict__ q) {
+    __shared__ V tile[CL][kPermRows + 1];
+    __shared__ uint32_t node[kPermRows];
+    __shared__ V scale[kPermRows];
+    constexpr int step = kPermRows / CL;       // rows of one load
+    const int alpha = blockIdx.y, tid = (int)threadIdx.x;
+    if (blockIdx.x == 0 && tid == 0 && r.xmask) r.xmask[(size_t)alpha * 32] = 0u;
     const SrcDev& sd = a.src[alpha];
     const uint64_t* __restrict__ meta = DIR == kFwd ? sd.fmeta : sd.rmeta;
-    const V* __restrict__ wts = (const V*)(DIR == kFwd ? sd.fwts : sd.rwts);
     const bool per_source = DIR == kRev || a.in_mode == FM_DS_PER_PAIR;
     const V* __restrict__ in = (const V*)a.in + (per_source ? (size_t)alpha * a.N * a.B : 0);
     V* __restrict__ dst = q + (size_t)alpha * a.N * a.B;
     const int64_t p0 = (int64_t)blockIdx.x * kPermRows;
     const int rows = (int)min((int64_t)kPermRows, a.N - p0);
-    for (int c0 = 0; c0 < a.B; c0 += kPermCols) {
-        const int cols = min(kPermCols, a.B - c0);
-        if (c0) __syncthreads();
-        for (int t = threadIdx.x; t < rows * cols; t += 256) {
-            const int i = t / cols, b = t - i * cols;
-            const uint32_t node = (uint32_t)(gld(meta + p0 + i) & kNodeMask);
-            V x = gld(in + (size_t)node * a.B + c0 + b);
-            if (DIR == kFwd) x = gld(wts + (size_t)(p0 + i) * 4) * x;
-            tile[b][i] = x;
-        }
+    // rows past the end repeat the last one
+    const int64_t mine = p0 + min(tid, rows - 1);
+    node[tid] = (uint32_t)(gld(meta + mine) & kNodeMask);
+    if (DIR == kFwd) scale[tid] = gld((const V*)sd.fwts + (size_t)mine * 4);
+    __syncthreads();
+    const int c = tid % CL, i0 = tid / CL;
+    for (int c0 = 0; c0 < a.B; c0 += CL) {
+        const int col = min(c0 + c, a.B - 1);
+        V x[CL];
+#pragma unroll
+        for (int k = 0; k < CL; ++k) x[k] = gld(in + (size_t)node[i0 + k * step] * a.B + col);
+#pragma unroll
+        for (int k = 0; k < CL; ++k) tile[c][i0 + k * step] = DIR == kFwd ? scale[i0 + k * step] * x[k] : x[k];
         __syncthreads();
-        for (int t = threadIdx.x; t < cols * rows; t += 256) {
-            const int g = t / rows, i = t - g * rows;
-            dst[(size_t)(c0 + g) * a.N + p0 + i] = tile[g][i];
-        }
+        if (tid < rows)
+#pragma unroll
+            for (int k = 0; k < CL; ++k)
+                if (c0 + k < a.B) dst[(size_t)(c0 + k) * a.N + p0 + tid] = tile[k][tid];
+        __syncthreads();
     }
 }
 
@@ -1293,8 +1301,12 @@ static void ring_inputs(const fm_batch* b, bool fwd, const ApplyArgs& a, const R
         return;
     }
     const dim3 grid((unsigned)((a.N + kPermRows - 1) / kPermRows), a.S);
-    if (fwd) hipLaunchKernelGGL((k_ring_q<kFwd, V>), grid, dim3(256), 0, b->stream, a, ra, (V*)r->q);
-    else hipLaunchKernelGGL((k_ring_q<kRev, V>), grid, dim3(256), 0, b->stream, a, ra, (V*)r->q);
+    // columns at a time: a whole row up to 16
+    const auto fn = a.B > 8   ? (fwd ? k_ring_q<kFwd, V, 16> : k_ring_q<kRev, V, 16>)
+                    : a.B > 4 ? (fwd ? k_ring_q<kFwd, V, 8> : k_ring_q<kRev, V, 8>)
+                    : a.B > 1 ? (fwd ? k_ring_q<kFwd, V, 4> : k_ring_q<kRev, V, 4>)
+                              : (fwd ? k_ring_q<kFwd, V, 1> : k_ring_q<kRev, V, 1>);
+    hipLaunchKernelGGL(fn, grid, dim3(kPermRows), 0, b->stream, a, ra, (V*)r->q);
 }
 
 bool ring_has(const RingPlan* r, bool fwd) { return r && r->C[fwd ? 0 : 1] > 0; }
