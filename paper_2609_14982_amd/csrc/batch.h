@@ -119,6 +119,7 @@ struct fm_batch {
     // node split (tun.split > 1)
     int32_t split_grid = 0, split_per_xcd = 0, split_items = 0, split_lds_rows = 0;
     int32_t split_rcv_lds = 0, split_stage_off = 0;
+    int32_t split_unroll_rev = 0;    // nodes per thread in flight of the transpose (tun.unroll: the primal's)
     size_t split_lds = 0;
     int64_t stage_rows = 0;
     void* stage = nullptr;           // [S][stage_rows][B] FP64 block right-hand sides

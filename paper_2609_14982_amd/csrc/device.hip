@@ -710,7 +710,7 @@ static hipError_t launch_split(const fm_batch* b, bool fwd, const ApplyArgs& a0)
     hipLaunchKernelGGL(k_split_reset, dim3(1), dim3(256), 0, b->stream, s, b->S);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int lpn = split_lpn(b), nt = b->tun.threads, u = b->tun.unroll;
+    const int lpn = split_lpn(b), nt = b->tun.threads, u = fwd ? b->tun.unroll : b->split_unroll_rev;
     const int mode = (!fwd && a.in_mode == FM_W_RECEIVERS ? 1 : 0) | (b->states[0]->stencil == 26 ? 2 : 0);
     if (b->prec == FM_FP64)
         return launch_split_v<double>(fwd, mode, lpn, nt, u, a, s, b->split_grid, b->split_lds, b->stream);
@@ -726,14 +726,20 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
     const int vw = fp64 ? 2 : 4;
     const int lpn = b->B % vw == 0 ? b->B / vw : 0;
     if (t.split == 1) return FM_OK;
-    // the node split defaults to 512 threads and batches of 256-384 nodes (a
-    // workgroup's share of a typical level in one round trip)
+    // The node split defaults to 512 threads and batches of 256-384 nodes (a
+    // workgroup's share of a typical level in one round trip).  The transpose
+    // with 8 lanes per node takes 128: its registers then leave more waves in
+    // flight on the wide levels that are left to this kernel, which the primal
+    // does not need.  Batches of 256 and 128, FP64, 16 right-hand sides:
+    // 201x201x101, 64 sources, J 23.4 and 24.7 ms, J^T 36.7 and 30.9;
+    // 161x161x81, 8 sources, J 5.6 and 6.1, J^T 7.7 and 6.9.
+    const bool cube = b->states[0]->stencil == 26;
     const int nt = asked.threads ? asked.threads : 512;
     const int u = asked.unroll ? asked.unroll : (lpn == 16 ? 2 : lpn == 8 ? 4 : 3);
-    const bool cube = b->states[0]->stencil == 26;
+    const int ur = !asked.unroll && lpn == 8 && nt == 512 && !cube ? 2 : u;
     const void* kf = split_kernel(0, fp64, cube, lpn, nt, u);
-    const void* kr = split_kernel(1, fp64, cube, lpn, nt, u);
-    const void* kq = split_kernel(2, fp64, cube, lpn, nt, u);
+    const void* kr = split_kernel(1, fp64, cube, lpn, nt, ur);
+    const void* kq = split_kernel(2, fp64, cube, lpn, nt, ur);
     const bool built = kf && kr && kq;
     if (t.split != 0 && t.split != 2 && t.split != 4 && t.split != 8 && t.split != 16) {
         set_error("split must be 0, 1, 2, 4, 8 or 16");
@@ -866,9 +872,17 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
         b->split_grid = (int32_t)(8 * slots);
         b->split_items = (int32_t)tot;
     } else if (P == 0) {
+        // 16 workgroups per source where that leaves each of them 150 nodes of
+        // a level: J + J^T with 8 and 16, FP64, 16 right-hand sides, 8 sources:
+        // 201x201x101 22.8 and 15.6 ms, 161x161x81 13.3 and 9.8; 16 sources on
+        // 141x141x71 (about 200 nodes each) 10.6 and 8.1.  (Narrower levels are
+        // the window walk's; the cube stencil, denser per node, keeps 8.)
+        int64_t levels = 0;
+        for (const HostState* st : b->states) levels += st->pk.L_f + st->pk.L_r;
+        const int64_t width = 2 * (int64_t)b->S * b->N / std::max<int64_t>(levels, 1);
         P = 1;
-        for (int c : {8, 4, 2})
-            if (fits(c)) { P = c; break; }
+        for (int c : {16, 8, 4, 2})
+            if (fits(c) && (c < 16 || (!cube && width >= 16 * 150))) { P = c; break; }
         if (P == 1) { t.split = 1; return FM_OK; }
     } else if (!fits(P)) {
         set_error("split %d needs %lld resident workgroups; the device holds %lld", P, (long long)(8 * per8 * P),
@@ -884,6 +898,7 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
     t.split = P;
     t.threads = nt;
     t.unroll = u;
+    b->split_unroll_rev = ur;
     t.balance = asked.balance;
     if (!asked.balance) {
         b->split_per_xcd = (int32_t)(per8 * P);
