@@ -326,8 +326,8 @@ int fm_batch_create(fm_state* const* states, int32_t S, int32_t B, int32_t preci
 
 /*
  * Schedule search (the autotuned level chunks of the batching step, §4.4):
- * for the LDS window walk where the default takes it (reported as a schedule
- * of zeros), the rhs-group kernel and every built node-split shape (threads, nodes
+ * for the default (reported as a schedule of zeros), the rhs-group kernel and
+ * every built node-split shape (threads, nodes
  * per thread in flight) with 2, 4, 8 or 16 workgroups per source that fits
  * the device, create a batch of the given states, run fm_apply_J and
  * fm_apply_JT once, then time reps more pairs with HIP events on hip_stream,

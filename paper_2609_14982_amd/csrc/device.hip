@@ -1631,7 +1631,7 @@ int autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision, v
         }
     }
     std::vector<fm_tuning> list;
-    list.push_back(fm_tuning{});                      // the window walk, where the library takes it
+    list.push_back(fm_tuning{});                      // the library's own choice: the window walk or a node split
     list.push_back(fm_tuning{0, 0, 0, 0, 0, 1, 0});   // rhs groups, library defaults
     const int vw = precision == FM_FP64 ? 2 : 4;
     const int lpn = B % vw == 0 ? B / vw : 0;
@@ -1664,7 +1664,6 @@ int autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision, v
         fm_batch* b = nullptr;
         if (batch_create(states, S, B, precision, &t, stream, &b) != FM_OK) continue;   // does not fit
         if (t.split > 1 && !t.balance && b->tun.split != t.split) { batch_free(b); continue; }
-        if (is_default(t) && !b->ring) { batch_free(b); continue; }   // one of the schedules below
         float m = -1.0f;
         rc = apply_J(b, ds, ds_mode, j_out, out_mode);
         if (rc == FM_OK) rc = apply_JT(b, w, w_mode, jt_out, jt_mode);
@@ -1678,7 +1677,7 @@ int autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision, v
                 m /= (float)reps;
         }
         if (rc == FM_OK) rc = batch_status(b);
-        const fm_tuning used = b->ring ? t : b->tun;   // zero fields ask for the window walk again
+        const fm_tuning used = is_default(t) ? t : b->tun;   // zero fields ask for the library's choice again
         batch_free(b);
         if (rc != FM_OK) break;
         if (m >= 0.0f) {

@@ -69,6 +69,12 @@ namespace {
 constexpr int kChunk = 16;          // iterations between convergence checks
 constexpr int kTile = 64;           // words of 64 nodes listed by one wave
 constexpr int kThreads = 256;
+// Words (all sources) up to which an iteration is one launch, k_eik_word.  A
+// whole solve with it and with the lists: 2-D 77x40, 3 sources (192 words) 1.2
+// and 2.2 ms, 401x201, 1 and 4 sources (1280, 5120) 4.8 and 7.6, 7.1 and 9.3, 16
+// (20480) 13.9 and 10.4; 3-D 41x41x25, 1 source (704) 1.7 and 2.3, 8 (5632) 4.6
+// and 3.7, 101x101x51, 8 (65536) 53 and 19.
+constexpr int64_t kSmall2 = 8192, kSmall3 = 2048;
 constexpr uint16_t kCopy = 1u << 15;   // list entry: the value is only copied
 
 struct EikDims {
@@ -234,7 +240,96 @@ __device__ __forceinline__ uint64_t shifted(const uint64_t* __restrict__ m, int6
     return a >> sh | b << (64 - sh);
 }
 
-// An iteration is two launches.  The first spreads the changed bits to their
+// Word i of the nodes with a changed face neighbour.
+template <int DIM>
+__device__ __forceinline__ uint64_t spread(const EikDims& d, const uint64_t* __restrict__ co,
+                                           const uint64_t* __restrict__ edge, int64_t i) {
+    uint64_t a = (shifted(co, i, d.W, 1) & edge[i]) | (shifted(co, i, d.W, -1) & edge[d.W + i]) |
+                 (shifted(co, i, d.W, d.n0) & edge[2 * d.W + i]) | (shifted(co, i, d.W, -d.n0) & edge[3 * d.W + i]);
+    if (DIM == 3) a |= shifted(co, i, d.W, d.n0 * d.n1) | shifted(co, i, d.W, -d.n0 * d.n1);
+    const int64_t left = d.N - i * 64;
+    if (left < 64) a &= left > 0 ? (1ull << left) - 1ull : 0ull;
+    return a;
+}
+
+// F(T) at a node that is no seed, or its value where that is lower.
+template <int DIM>
+__device__ __forceinline__ double recompute(const EikDims& d, const double* __restrict__ X, const double* __restrict__ s,
+                                            const double* __restrict__ Told, uint32_t p32, double told) {
+    const uint32_t n0 = (uint32_t)d.n0, n1 = (uint32_t)d.n1, n2 = (uint32_t)d.n2;
+    const int64_t stride[3] = {1, d.n0, d.n0 * d.n1}, p = p32;
+    const uint32_t nn[3] = {n0, n1, n2};
+    const uint32_t r = p32 / n0;
+    const uint32_t c[3] = {p32 - r * n0, r % n1, r / n1};
+    int64_t nb[DIM][2];
+    for (int k = 0; k < DIM; ++k) {
+        nb[k][0] = c[k] > 0 ? p - stride[k] : -1;
+        nb[k][1] = c[k] < nn[k] - 1 ? p + stride[k] : -1;
+    }
+    const double si = s[p];
+    double xi[3], xk[DIM][2][3], tk[DIM][2];
+    for (int k = 0; k < DIM; ++k) xi[k] = X[p * DIM + k];
+    double best = INFINITY;
+    for (int k = 0; k < DIM; ++k)
+        for (int side = 0; side < 2; ++side) {
+            const int64_t q = nb[k][side];
+            tk[k][side] = q >= 0 ? Told[q] : INFINITY;
+            for (int m = 0; m < DIM; ++m) xk[k][side][m] = q >= 0 ? X[q * DIM + m] : 0.0;
+            if (q >= 0) best = fmin(best, tk[k][side] + si * dist(xi, xk[k][side], DIM));
+        }
+    // a simplex whose vertex values are all >= best cannot lower it:
+    // its interior values exceed its least vertex value
+    for (int a = 0; a < DIM; ++a)
+        for (int b = a + 1; b < DIM; ++b)
+            for (int sa = 0; sa < 2; ++sa)
+                for (int sb = 0; sb < 2; ++sb)
+                    if (nb[a][sa] >= 0 && nb[b][sb] >= 0 && fmin(tk[a][sa], tk[b][sb]) < best)
+                        best = fmin(best, seg_inner(xi, si, xk[a][sa], tk[a][sa], xk[b][sb], tk[b][sb], DIM));
+    if constexpr (DIM == 3) {
+        for (int s0 = 0; s0 < 2; ++s0)
+            for (int s1 = 0; s1 < 2; ++s1)
+                for (int s2 = 0; s2 < 2; ++s2)
+                    if (nb[0][s0] >= 0 && nb[1][s1] >= 0 && nb[2][s2] >= 0 &&
+                        fmin(fmin(tk[0][s0], tk[1][s1]), tk[2][s2]) < best)
+                        best = fmin(best, tri_inner(xi, si, xk[0][s0], tk[0][s0], xk[1][s1], tk[1][s1],
+                                                    xk[2][s2], tk[2][s2]));
+    }
+    return fmin(told, best);
+}
+
+// One iteration in one launch, a wave per word and a lane per node: for small
+// grids, where a second launch costs more than the lanes without work.
+template <int DIM>
+__global__ __launch_bounds__(64) void k_eik_word(EikDims d, int32_t S, const double* __restrict__ X,
+                                                 const double* __restrict__ s, const double* __restrict__ Told_,
+                                                 double* __restrict__ Tnew_, const uint64_t* __restrict__ cold,
+                                                 uint64_t* __restrict__ cnew, const uint64_t* __restrict__ seeds,
+                                                 const uint64_t* __restrict__ edge, unsigned* __restrict__ n_batch) {
+    const int lane = (int)threadIdx.x;
+    for (int64_t w = blockIdx.x; w < (int64_t)S * d.W; w += gridDim.x) {
+        const int64_t alpha = w / d.W, i = w - alpha * d.W;
+        const uint64_t* __restrict__ co = cold + alpha * d.W;
+        const uint64_t open = ~seeds[w];
+        const uint64_t a = spread<DIM>(d, co, edge, i) & open, t = a | (co[i] & open);
+        const double* __restrict__ Told = Told_ + alpha * d.N;
+        double* __restrict__ Tnew = Tnew_ + alpha * d.N;
+        bool changed = false;
+        if (t >> lane & 1ull) {
+            const uint32_t p = (uint32_t)(i * 64) + (uint32_t)lane;
+            const double told = Told[p];
+            const double v = a >> lane & 1ull ? recompute<DIM>(d, X, s, Told, p, told) : told;
+            Tnew[p] = v;
+            changed = v != told;
+        }
+        const uint64_t ch = __ballot(changed);
+        if (lane == 0) {
+            cnew[w] = ch;
+            if (t) *n_batch = 1u;      // (every wave stores the same)
+        }
+    }
+}
+
+// On other grids an iteration is two launches.  The first spreads the changed bits to their
 // face neighbours (a few words per 64 nodes) and lists the nodes to recompute,
 // one wave per tile of 64 words: the tile's nodes in order, and a batch for
 // every 64 of them, so that the second launch finds all its work in full waves
@@ -261,13 +356,8 @@ __global__ __launch_bounds__(kThreads) void k_eik_list(EikDims d, int32_t S, con
         if (tile < tiles) {
             const int64_t alpha = tile / (d.W / kTile), i = (tile - alpha * (d.W / kTile)) * kTile + lane;
             const uint64_t* __restrict__ co = cold + alpha * d.W;
-            uint64_t a = (shifted(co, i, d.W, 1) & edge[i]) | (shifted(co, i, d.W, -1) & edge[d.W + i]) |
-                         (shifted(co, i, d.W, d.n0) & edge[2 * d.W + i]) | (shifted(co, i, d.W, -d.n0) & edge[3 * d.W + i]);
-            if (DIM == 3) a |= shifted(co, i, d.W, d.n0 * d.n1) | shifted(co, i, d.W, -d.n0 * d.n1);
-            const int64_t left = d.N - i * 64;
-            if (left < 64) a &= left > 0 ? (1ull << left) - 1ull : 0ull;
             const uint64_t open = ~seeds[alpha * d.W + i];
-            a &= open;
+            const uint64_t a = spread<DIM>(d, co, edge, i) & open;
             const uint64_t t = a | (co[i] & open);
             cnew[alpha * d.W + i] = 0ull;
             int n = __popcll(t);       // running sum over the lanes
@@ -313,9 +403,6 @@ __global__ __launch_bounds__(64, 3) void k_eik_step(EikDims d, const double* __r
                                                  const uint32_t* __restrict__ batch, const unsigned* __restrict__ n_batch) {
     __shared__ unsigned long long ch[kTile];           // changed nodes of the batch's tile
     const int lane = (int)threadIdx.x;
-    const uint32_t n0 = (uint32_t)d.n0, n1 = (uint32_t)d.n1, n2 = (uint32_t)d.n2;
-    const int64_t stride[3] = {1, d.n0, d.n0 * d.n1};
-    const uint32_t nn[3] = {n0, n1, n2};
     const uint32_t tps = (uint32_t)(d.W / kTile);      // tiles per source
     const unsigned n_b = *n_batch;
     ch[lane] = 0ull;
@@ -334,43 +421,7 @@ __global__ __launch_bounds__(64, 3) void k_eik_step(EikDims d, const double* __r
                 // the same value unless the node changed in the last iteration
                 Tnew[p] = Told[p];
             } else {
-                const uint32_t r = p32 / n0;
-                const uint32_t c[3] = {p32 - r * n0, r % n1, r / n1};
-                int64_t nb[DIM][2];
-                for (int k = 0; k < DIM; ++k) {
-                    nb[k][0] = c[k] > 0 ? p - stride[k] : -1;
-                    nb[k][1] = c[k] < nn[k] - 1 ? p + stride[k] : -1;
-                }
-                const double told = Told[p];
-                const double si = s[p];
-                double xi[3], xk[DIM][2][3], tk[DIM][2];
-                for (int k = 0; k < DIM; ++k) xi[k] = X[p * DIM + k];
-                double best = INFINITY;
-                for (int k = 0; k < DIM; ++k)
-                    for (int side = 0; side < 2; ++side) {
-                        const int64_t q = nb[k][side];
-                        tk[k][side] = q >= 0 ? Told[q] : INFINITY;
-                        for (int m = 0; m < DIM; ++m) xk[k][side][m] = q >= 0 ? X[q * DIM + m] : 0.0;
-                        if (q >= 0) best = fmin(best, tk[k][side] + si * dist(xi, xk[k][side], DIM));
-                    }
-                // a simplex whose vertex values are all >= best cannot lower it:
-                // its interior values exceed its least vertex value
-                for (int a = 0; a < DIM; ++a)
-                    for (int b = a + 1; b < DIM; ++b)
-                        for (int sa = 0; sa < 2; ++sa)
-                            for (int sb = 0; sb < 2; ++sb)
-                                if (nb[a][sa] >= 0 && nb[b][sb] >= 0 && fmin(tk[a][sa], tk[b][sb]) < best)
-                                    best = fmin(best, seg_inner(xi, si, xk[a][sa], tk[a][sa], xk[b][sb], tk[b][sb], DIM));
-                if constexpr (DIM == 3) {
-                    for (int s0 = 0; s0 < 2; ++s0)
-                        for (int s1 = 0; s1 < 2; ++s1)
-                            for (int s2 = 0; s2 < 2; ++s2)
-                                if (nb[0][s0] >= 0 && nb[1][s1] >= 0 && nb[2][s2] >= 0 &&
-                                    fmin(fmin(tk[0][s0], tk[1][s1]), tk[2][s2]) < best)
-                                    best = fmin(best, tri_inner(xi, si, xk[0][s0], tk[0][s0], xk[1][s1], tk[1][s1],
-                                                                xk[2][s2], tk[2][s2]));
-                }
-                const double v = fmin(told, best);
+                const double told = Told[p], v = recompute<DIM>(d, X, s, Told, p32, told);
                 Tnew[p] = v;
                 if (v != told) atomicOr(&ch[p32 >> 6 & (kTile - 1)], 1ull << (p32 & 63u));
             }
@@ -510,16 +561,25 @@ int fm_eikonal_solve(fm_eikonal* e, const double* s, int32_t S, const double* xi
     hipLaunchKernelGGL(k_eik_init, dim3(grid), dim3(256), 0, st, d, S, e->X, s, e->xi, seed_radius, buf[0], buf[1],
                        e->chg[0], e->seed);
     HIP_TRY(hipGetLastError());
+    const auto list_fn = e->dim == 3 ? k_eik_list<3> : k_eik_list<2>;
+    const auto step_fn = e->dim == 3 ? k_eik_step<3> : k_eik_step<2>;
+    const auto word_fn = e->dim == 3 ? k_eik_word<3> : k_eik_word<2>;
+    const int64_t words = (int64_t)S * e->W;
+    const bool small = words <= (e->dim == 3 ? kSmall3 : kSmall2);
     int cur = 0;
     int32_t done = 0;
     while (done < max_iter) {
         const int n = std::min<int32_t>(kChunk, max_iter - done);
         hipLaunchKernelGGL(k_clear_counts, dim3(1), dim3(64), 0, st, e->n_batch);
-        const auto list_fn = e->dim == 3 ? k_eik_list<3> : k_eik_list<2>;
-        const auto step_fn = e->dim == 3 ? k_eik_step<3> : k_eik_step<2>;
         // an iteration changed nothing when the next list is empty: one more
         // list follows the chunk (its iteration lists the same again)
         for (int j = 0; j <= n; j++) {
+            if (small && j < n) {
+                hipLaunchKernelGGL(word_fn, dim3((unsigned)words), dim3(64), 0, st, d, S, e->X, s, buf[cur], buf[cur ^ 1],
+                                   e->chg[cur], e->chg[cur ^ 1], e->seed, e->edge, e->n_batch + j);
+                cur ^= 1;
+                continue;
+            }
             hipLaunchKernelGGL(list_fn, dim3(tiles), dim3(kThreads), 0, st, d, S, e->chg[cur], e->chg[cur ^ 1],
                                e->seed, e->edge, e->list, e->count, e->batch, e->n_batch + j);
             if (j == n) break;
