@@ -872,17 +872,16 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
         b->split_grid = (int32_t)(8 * slots);
         b->split_items = (int32_t)tot;
     } else if (P == 0) {
-        // 16 workgroups per source where that leaves each of them 150 nodes of
-        // a level: J + J^T with 8 and 16, FP64, 16 right-hand sides, 8 sources:
-        // 201x201x101 22.8 and 15.6 ms, 161x161x81 13.3 and 9.8; 16 sources on
-        // 141x141x71 (about 200 nodes each) 10.6 and 8.1.  (Narrower levels are
-        // the window walk's; the cube stencil, denser per node, keeps 8.)
-        int64_t levels = 0;
-        for (const HostState* st : b->states) levels += st->pk.L_f + st->pk.L_r;
-        const int64_t width = 2 * (int64_t)b->S * b->N / std::max<int64_t>(levels, 1);
+        // At most 8 workgroups a source, so that up to 16 sources take half of
+        // the card and the applies of two such batches on two streams are
+        // resident together.  (16 are faster where a level is wide, J + J^T,
+        // FP64, 16 right-hand sides, 8 sources: 201x201x101 22.8 and 15.6 ms,
+        // 161x161x81 13.3 and 9.8; but 9 to 16 sources then fill the card, and two
+        // batches that are each partly resident wait for each other until the
+        // bounded waits give up.  A caller may ask for them.)
         P = 1;
-        for (int c : {16, 8, 4, 2})
-            if (fits(c) && (c < 16 || (!cube && width >= 16 * 150))) { P = c; break; }
+        for (int c : {8, 4, 2})
+            if (fits(c)) { P = c; break; }
         if (P == 1) { t.split = 1; return FM_OK; }
     } else if (!fits(P)) {
         set_error("split %d needs %lld resident workgroups; the device holds %lld", P, (long long)(8 * per8 * P),
