@@ -764,16 +764,27 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
     // caller's request, or 16 KB, two 256-thread workgroups fit on a CU)
     const int64_t lds_cap = (int64_t)kLdsMax - 1024;
     const size_t lds = (size_t)std::min<int64_t>(std::max<int64_t>(asked.min_lds_bytes, 16 * 1024), lds_cap);
+    // receiver inputs of the transpose in LDS when they fit in 64 KB (values
+    // as FP64, then the int32 positions), the block staging area after them
+    size_t n_ent = 0;
+    for (HostState* st : b->states) n_ent = std::max(n_ent, st->pk.rcv_node.size());
+    const size_t rcv_bytes = n_ent * b->B * sizeof(double) + n_ent * sizeof(int32_t);
+    b->split_rcv_lds = n_ent > 0 && rcv_bytes <= 64 * 1024;
+    b->split_stage_off = b->split_rcv_lds ? (int32_t)(((rcv_bytes + 255) & ~(size_t)255) / sizeof(double)) : 0;
+    const size_t lds_all = std::min<size_t>(lds + (size_t)b->split_stage_off * sizeof(double), (size_t)lds_cap);
     int dev = b->device, cus = 0;
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    int occ = 1 << 30;
+    // workgroups resident at once without and with the receiver inputs' LDS
+    int occ = 1 << 30, occ_all = 1 << 30;
     for (const void* k : {kf, kr, kq}) {
         HIP_TRY(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_cap));
         int nb = 0;
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, nt, lds));
         occ = std::min(occ, nb);
+        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, nt, lds_all));
+        occ_all = std::min(occ_all, nb);
     }
-    const int64_t cap = (int64_t)occ * cus;
+    const int64_t cap = (int64_t)occ * cus, cap_all = (int64_t)occ_all * cus;
     const int64_t per8 = (b->S + 7) / 8;
     auto fits = [&](int P) { return 8 * per8 * P <= cap; };
     int P = t.split;
@@ -872,7 +883,8 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
         b->split_grid = (int32_t)(8 * slots);
         b->split_items = (int32_t)tot;
     } else if (P == 0) {
-        // At most 8 workgroups a source, so that up to 16 sources take half of
+        // The most that is resident with the LDS of the launch, and at most 8
+        // workgroups a source, so that up to 16 sources take half of
         // the card and the applies of two such batches on two streams are
         // resident together.  (16 are faster where a level is wide, J + J^T,
         // FP64, 16 right-hand sides, 8 sources: 201x201x101 22.8 and 15.6 ms,
@@ -881,7 +893,7 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
         // bounded waits give up.  A caller may ask for them.)
         P = 1;
         for (int c : {8, 4, 2})
-            if (fits(c)) { P = c; break; }
+            if (8 * per8 * c <= cap_all) { P = c; break; }
         if (P == 1) { t.split = 1; return FM_OK; }
     } else if (!fits(P)) {
         set_error("split %d needs %lld resident workgroups; the device holds %lld", P, (long long)(8 * per8 * P),
@@ -904,24 +916,12 @@ static int prepare_split(fm_batch* b, fm_tuning& t, const fm_tuning& asked) {
         b->split_grid = 8 * b->split_per_xcd;
         b->split_items = b->S * P;
     }
-    // receiver inputs of the transpose in LDS when they fit in 64 KB (values
-    // as FP64, then the int32 positions), the block staging area after them
-    size_t n_ent = 0;
-    for (HostState* st : b->states) n_ent = std::max(n_ent, st->pk.rcv_node.size());
-    const size_t rcv_bytes = n_ent * b->B * sizeof(double) + n_ent * sizeof(int32_t);
-    b->split_rcv_lds = n_ent > 0 && rcv_bytes <= 64 * 1024;
-    b->split_stage_off = b->split_rcv_lds ? (int32_t)(((rcv_bytes + 255) & ~(size_t)255) / sizeof(double)) : 0;
-    const size_t lds_all = std::min<size_t>(lds + (size_t)b->split_stage_off * sizeof(double), (size_t)lds_cap);
     b->split_lds = lds_all;
     t.min_lds_bytes = (int32_t)lds;
     b->split_lds_rows = (int32_t)((lds_all - (size_t)b->split_stage_off * sizeof(double)) / ((size_t)b->B * sizeof(double)));
-    for (const void* k : {kf, kr, kq}) {
-        int nb = 0;
-        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, nt, lds_all));
-        if ((int64_t)nb * cus < b->split_grid) {
-            set_error("node split: the workgroups no longer fit with %zu B of LDS", lds_all);
-            return FM_EINVAL;
-        }
+    if (cap_all < b->split_grid) {
+        set_error("node split: the workgroups no longer fit with %zu B of LDS", lds_all);
+        return FM_EINVAL;
     }
     b->stage_rows = rows;
     if (b->split_lds_rows < 1) { set_error("LDS too small for one staged row"); return FM_EINVAL; }

@@ -56,3 +56,28 @@ def test_two_default_batches_fit_on_two_streams(wide, S, B):
         assert torch.equal(y[i], y[2]) and torch.equal(g[i], g[2])
     for b in batches:
         b.free()
+
+
+@pytest.mark.parametrize("S", [16, 24, 40])
+def test_receiver_inputs_count_in_the_choice(S):
+    """256-thread workgroups, two per CU until the receiver inputs (124 of four
+    entries, 16 columns, 64 KB) leave LDS for one: the default takes fewer."""
+    wl = W.flat_radial(21, 21, 11)
+    wl.rcv, wl.rcv_w, _ = W.interpolating_receivers(wl, 124, 62)
+    state = states_for(fm, wl)[0]
+    print(f"case receiver inputs 21x21x11 S={S}", flush=True)
+    B = 16
+    b = fm.Batch([state] * S, B, fm.FM_FP64, tuning={"threads": 256})
+    assert b.tuning()["split"] > 1 and 8 * ((S + 7) // 8) * b.tuning()["split"] <= CARD
+    one = fm.Batch([state], B, fm.FM_FP64, tuning={"split": 1})
+    rng = np.random.default_rng(63)
+    w = torch.from_numpy(rng.standard_normal((1, b.R, B))).cuda()
+    got = torch.empty(S, b.N, B, dtype=torch.float64, device="cuda")
+    ref = torch.empty(1, b.N, B, dtype=torch.float64, device="cuda")
+    b.apply_JT(w.expand(S, -1, -1).contiguous(), fm.FM_W_RECEIVERS, got, fm.FM_JT_PER_SOURCE)
+    one.apply_JT(w, fm.FM_W_RECEIVERS, ref, fm.FM_JT_PER_SOURCE)
+    b.status()
+    one.status()
+    assert torch.linalg.norm(got - ref) <= 1e-13 * torch.linalg.norm(ref.expand_as(got))
+    b.free()
+    one.free()
