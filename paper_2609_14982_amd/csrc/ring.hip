@@ -113,8 +113,12 @@ __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0
 
 // every load and store of this wave has completed (vmcnt(0) alone, as a
 // builtin: the compiler then knows it too, and the waits after the branch stay
-// those of the other path)
-__device__ __forceinline__ void drain() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+// those of the other path).  The wait names no memory: the fence before it
+// keeps the compiler from moving a store past it.
+__device__ __forceinline__ void drain() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+}
 
 __device__ __forceinline__ uint32_t uni(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 
