@@ -143,14 +143,16 @@ struct WalkCtx {
     const SrcDev* sd;
     const RingDev* rd;
     const void* q;            // this item's inputs in level order, or nullptr
+    const V* in;              // primal: rows of ds, at this group's first value
     uint32_t lds;             // LDS address of the window
     int stage_off;
 };
 
-// The blocks of level l, by all TB threads: right-hand sides b (FP64)
-// from the window, then rows of A_C^{-1} b; the columns of a block are split
-// over groups of whole waves when it has fewer rows than the workgroup has
-// threads, and the partial sums added in column order.
+// The blocks of level l, by all TB threads: right-hand sides b from the window
+// (summed in FP64 whatever the vector precision), then rows of A_C^{-1} b; the
+// columns of a block are split over groups of whole waves when it has fewer
+// rows than the workgroup has threads, and the partial sums added in column
+// order.
 template <int DIR, typename V, int RG, int TB, bool QS>
 __device__ __forceinline__ void ring_blocks(const WalkCtx<V>& w) {
     typedef Pack<V, RG> P;
@@ -201,9 +203,17 @@ __device__ __forceinline__ void ring_blocks(const WalkCtx<V>& w) {
             const uint32_t* rf = rd.wref + (size_t)(w0 + m) * 4;
             const V* wt = wwt + (size_t)(w0 + m) * 8;
             double acc[RG];
-            const P r = QS ? rd_win(gld(reinterpret_cast<const uint32_t*>(wt + 7))) : glv(q + bp + m);
+            if constexpr (DIR == kFwd && sizeof(V) == 4) {
+                // (c ds is exact in FP64; the input pass has rounded it to FP32)
+                const V* ds = w.in + (size_t)(gld(rf) & ~kStore) * w.oB;
+                const double c = (double)gld(wt);
 #pragma unroll
-            for (int v = 0; v < RG; ++v) acc[v] = (double)r.v[v];
+                for (int v = 0; v < RG; ++v) acc[v] = c * (double)gld(ds + v);
+            } else {
+                const P r = QS ? rd_win(gld(reinterpret_cast<const uint32_t*>(wt + 7))) : glv(q + bp + m);
+#pragma unroll
+                for (int v = 0; v < RG; ++v) acc[v] = (double)r.v[v];
+            }
 #pragma unroll
             for (int t = 0; t < 6; ++t) {
                 const uint32_t s = (gld(rf + 1 + t / 2) >> (16 * (t & 1))) & 0xffffu;
@@ -602,6 +612,7 @@ __global__ __launch_bounds__((CW + OW + FW) * 64) void k_ring(ApplyArgs a, RingA
     w.sd = a.src + alpha;
     w.rd = r.dev + 2 * alpha + (DIR == kFwd ? 0 : 1);
     w.q = q;
+    w.in = DIR == kFwd ? (const V*)a.in + (a.in_mode == FM_DS_PER_PAIR ? (size_t)alpha * a.N * a.B : 0) + rhs0 : nullptr;
     w.lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring_lds;
     w.stage_off = r.stage_off;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
