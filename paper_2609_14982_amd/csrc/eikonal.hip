@@ -304,7 +304,7 @@ __global__ __launch_bounds__(64) void k_eik_word(EikDims d, int32_t S, const dou
                                                  const double* __restrict__ s, const double* __restrict__ Told_,
                                                  double* __restrict__ Tnew_, const uint64_t* __restrict__ cold,
                                                  uint64_t* __restrict__ cnew, const uint64_t* __restrict__ seeds,
-                                                 const uint64_t* __restrict__ edge, unsigned* __restrict__ n_batch) {
+                                                 const uint64_t* __restrict__ edge, unsigned* __restrict__ any) {
     const int lane = (int)threadIdx.x;
     for (int64_t w = blockIdx.x; w < (int64_t)S * d.W; w += gridDim.x) {
         const int64_t alpha = w / d.W, i = w - alpha * d.W;
@@ -324,7 +324,7 @@ __global__ __launch_bounds__(64) void k_eik_word(EikDims d, int32_t S, const dou
         const uint64_t ch = __ballot(changed);
         if (lane == 0) {
             cnew[w] = ch;
-            if (t) *n_batch = 1u;      // (every wave stores the same)
+            if (ch) *any = 1u;         // (every wave stores the same)
         }
     }
 }
@@ -571,15 +571,13 @@ int fm_eikonal_solve(fm_eikonal* e, const double* s, int32_t S, const double* xi
     while (done < max_iter) {
         const int n = std::min<int32_t>(kChunk, max_iter - done);
         hipLaunchKernelGGL(k_clear_counts, dim3(1), dim3(64), 0, st, e->n_batch);
-        // an iteration changed nothing when the next list is empty: one more
-        // list follows the chunk (its iteration lists the same again)
-        for (int j = 0; j <= n; j++) {
-            if (small && j < n) {
-                hipLaunchKernelGGL(word_fn, dim3((unsigned)words), dim3(64), 0, st, d, S, e->X, s, buf[cur], buf[cur ^ 1],
-                                   e->chg[cur], e->chg[cur ^ 1], e->seed, e->edge, e->n_batch + j);
-                cur ^= 1;
-                continue;
-            }
+        // word j + 1 stays 0 when iteration j changed nothing: on small grids the
+        // iteration writes it; otherwise it is the length of the next list, and
+        // one more list follows the chunk (its iteration lists the same again)
+        for (int j = 0; small && j < n; j++, cur ^= 1)
+            hipLaunchKernelGGL(word_fn, dim3((unsigned)words), dim3(64), 0, st, d, S, e->X, s, buf[cur], buf[cur ^ 1],
+                               e->chg[cur], e->chg[cur ^ 1], e->seed, e->edge, e->n_batch + j + 1);
+        for (int j = 0; !small && j <= n; j++) {
             hipLaunchKernelGGL(list_fn, dim3(tiles), dim3(kThreads), 0, st, d, S, e->chg[cur], e->chg[cur ^ 1],
                                e->seed, e->edge, e->list, e->count, e->batch, e->n_batch + j);
             if (j == n) break;
