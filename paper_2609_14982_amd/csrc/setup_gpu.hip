@@ -34,6 +34,7 @@
 #include "fmbtf.h"
 #include "internal.h"
 #include "batch.h"
+#include "devmem.h"
 
 namespace fm {
 
@@ -451,31 +452,6 @@ struct LevelServer {
     }
 };
 
-// One device allocation for several arrays.  hipMalloc and hipFree take 0.2 ms
-// each and one at a time whichever thread calls them: with an allocation per
-// array, 8 sources on 101x101x51 spent 54 ms of a 165 ms pass (setup, batch, one
-// J^T) in 215 hipFree calls alone.
-struct Part {
-    void** p;
-    size_t bytes;
-};
-
-hipError_t carve(void** block, const std::vector<Part>& parts) {
-    size_t total = 0;
-    for (const Part& x : parts) total += (x.bytes + 255) & ~size_t(255);
-    const hipError_t e = hipMalloc(block, std::max<size_t>(total, 256));
-    if (e != hipSuccess) {
-        *block = nullptr;
-        return e;
-    }
-    char* at = (char*)*block;
-    for (const Part& x : parts) {
-        *x.p = at;
-        at += (x.bytes + 255) & ~size_t(255);
-    }
-    return hipSuccess;
-}
-
 // Per host thread: a stream, device buffers and pinned host staging for the
 // condensation levels and the records of the states it finishes.
 struct LevelCtx {
@@ -498,24 +474,25 @@ struct LevelCtx {
     // pass (not owned)
     const double *src_w6 = nullptr, *src_cal = nullptr;
     const uint8_t* src_pm = nullptr;
-    void* block = nullptr;       // holds every array above but w6 and cal
+    DevBlocks block;             // holds every array above but w6 and cal
     // the arrays for components numbered below c on a grid of N nodes
     hipError_t reserve(int64_t c, int64_t N) {
         const size_t n = (size_t)N, k = (size_t)c, i = sizeof(int32_t);
-        const hipError_t e = carve(&block, {{(void**)&cid, i * k}, {(void**)&bmem, i * k}, {(void**)&cnt, i * k},
-                                            {(void**)&f0, i * k}, {(void**)&f1, i * k}, {(void**)&lf, i * k},
-                                            {(void**)&lr, i * k}, {(void**)&cnt_r, i * k}, {(void**)&f0_r, i * k},
-                                            {(void**)&f1_r, i * k}, {(void**)&bptr, i * (k + 1)}, {(void**)&pm, n},
-                                            {(void**)&sm, n}, {(void**)&pos, i * n}, {(void**)&comp, i * n},
-                                            {(void**)&bsum, i * ((n + 1023) / 1024 + 1)}, {(void**)&rcv, n},
-                                            {(void**)&extm, n}});
+        const hipError_t e = block.take({{(void**)&cid, i * k}, {(void**)&bmem, i * k}, {(void**)&cnt, i * k},
+                                         {(void**)&f0, i * k}, {(void**)&f1, i * k}, {(void**)&lf, i * k},
+                                         {(void**)&lr, i * k}, {(void**)&cnt_r, i * k}, {(void**)&f0_r, i * k},
+                                         {(void**)&f1_r, i * k}, {(void**)&bptr, i * (k + 1)}, {(void**)&pm, n},
+                                         {(void**)&sm, n}, {(void**)&pos, i * n}, {(void**)&comp, i * n},
+                                         {(void**)&bsum, i * ((n + 1023) / 1024 + 1)}, {(void**)&rcv, n},
+                                         {(void**)&extm, n}});
         if (e == hipSuccess) cap = c;
+        else block.release();
         return e;
     }
     void release() {
-        for (void* p : {block, (void*)w6, (void*)cal})
+        for (void* p : {(void*)w6, (void*)cal})
             if (p) (void)hipFree(p);
-        block = nullptr;
+        block.release();
         if (host) (void)hipHostFree(host);
         if (stream) (void)hipStreamDestroy(stream);
         cid = bptr = bmem = cnt = f0 = f1 = lf = lr = nullptr;
@@ -637,7 +614,7 @@ int device_pack(void* ctxp, bool fwd, int64_t N, const int32_t* pos_of, const in
     hipError_t e = hipSuccess;
     if (!x.stream) e = hipStreamCreateWithFlags(&x.stream, hipStreamNonBlocking);
     const int64_t nb = (N + 1023) / 1024;
-    if (e == hipSuccess && !x.block) e = x.reserve(N, N);
+    if (e == hipSuccess && x.block.blocks.empty()) e = x.reserve(N, N);
     if (e == hipSuccess && !x.src_w6 && !x.w6) e = hipMalloc(&x.w6, sizeof(double) * 6 * (size_t)N);
     if (e == hipSuccess && !x.src_cal && !x.cal) e = hipMalloc(&x.cal, sizeof(double) * (size_t)N);
     hipStream_t s = x.stream;
@@ -878,7 +855,7 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
     uint8_t *dm = nullptr, *dsm = nullptr, *dtr = nullptr;
     int32_t *dcnt = nullptr, *df0 = nullptr, *df1 = nullptr, *dlf = nullptr, *dlr = nullptr;
     int32_t *dcnt_r = nullptr, *df0_r = nullptr, *df1_r = nullptr;
-    void* block = nullptr;       // holds all of these
+    DevBlocks block;             // holds all of these
     int64_t* dsrc = nullptr;
     unsigned long long* dnv = nullptr;
     int* dbad = nullptr;
@@ -891,7 +868,7 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
         x.server = &server;
     }
     auto release = [&]() {
-        if (block) (void)hipFree(block);
+        block.release();
         for (LevelCtx& x : lctx) x.release();
         if (hst) (void)hipHostFree(hst);
     };
@@ -910,8 +887,9 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
                                {(void**)&dbad, sizeof(int) * S}};
     for (int32_t** p : {&dcnt, &df0, &df1, &dlf, &dlr, &dcnt_r, &df0_r, &df1_r})
         parts.push_back({(void**)p, sizeof(int32_t) * nc});
-    if (e == hipSuccess) e = carve(&block, parts);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&hst, (size_t)N * chunk * (2 + 7 * sizeof(double)));
+    if (e == hipSuccess) e = block.take(parts);
+    const size_t staging = nc * (2 + 7 * sizeof(double));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&hst, staging);
     if (e == hipSuccess) e = hipMemcpy(dG, g->G, sizeof(double) * (size_t)N * d.ncomp_g, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(ds, s, sizeof(double) * (size_t)N, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(dsrc, src_nodes, sizeof(int64_t) * S, hipMemcpyHostToDevice);
@@ -1051,7 +1029,7 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
         // (their device work then needs no upload); without the memory for
         // it the host thread uploads them
         const size_t copy = ((size_t)N * (6 * sizeof(double) + sizeof(double) + 1) + 255) & ~size_t(255);
-        if (a0 == 0) {
+        if (a0 == 0 && copy > (size_t(2) << 20)) {      // (devmem.h)
             void* p = nullptr;
             if (hipMalloc(&p, copy * (size_t)n) == hipSuccess) {
                 std::lock_guard<std::mutex> lk(pool_mu);
