@@ -48,6 +48,7 @@
 #include <new>
 #include <vector>
 
+#include "devmem.h"
 #include "ring.h"
 #include "sweep.h"
 
@@ -722,6 +723,15 @@ struct BuildArgs {
     int32_t C[kCand];
 };
 
+// (kernels: a memset costs the host 35 us)
+__global__ void k_ring_clear(BuildArgs a) {
+    const BuildDev& d = a.dev[blockIdx.y];
+    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < a.N; p += (int64_t)gridDim.x * blockDim.x) {
+        d.pos[p] = -1;
+        d.need[p] = 0;
+    }
+}
+
 __global__ void k_ring_pos(BuildArgs a) {
     const BuildDev& d = a.dev[blockIdx.y];
     const int64_t n = d.lvl_ptr[d.L];
@@ -847,7 +857,9 @@ __global__ __launch_bounds__(256) void k_ring_fill(BuildArgs a) {
             *reinterpret_cast<uint32_t*>(o + 7) = qs;
         }
     }
-    // a counted receiver without entries leaves its place unused
+    // a counted receiver without entries leaves its place unused; lanes without
+    // an entry load the one past the end
+    if (l == d.L - 1 && threadIdx.x == 0) d.far[d.lv[d.L].y] = 0u;
     __syncthreads();
     for (int32_t i = n_far + (int32_t)threadIdx.x; i < lv_end(d, l); i += 256) d.far[lv.y + i] = 0u;
 }
@@ -867,15 +879,14 @@ struct RingPlan {
     size_t lds = 0;
     int32_t stage_off = 0;
     bool pt = false;              // off-grid sources: the seed transposes read every row
-    void* blob = nullptr;         // tables
-    RingDev* dev = nullptr;       // [S][2], inside blob
+    DevBlocks mem;                // the tables and q
+    RingDev* dev = nullptr;       // [S][2]
     void* q = nullptr;            // inputs in level order
 };
 
 void ring_free(RingPlan* r) {
     if (!r) return;
-    if (r->blob) (void)hipFree(r->blob);
-    if (r->q) (void)hipFree(r->q);
+    r->mem.release();
     delete r;
 }
 
@@ -976,7 +987,6 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     // far references need the same positions in every direction of every
     // source: temporary buffers of the passes below
     Bytes tb;
-    std::vector<size_t> o_pos(nd), o_need(nd), o_cnt(nd);
     std::vector<BuildDev> bd(nd);
     // levels in chunks of at most `chunk` singletons, the level's blocks with its
     // last chunk: each is a step of the walk of its own, so that a wide level
@@ -997,11 +1007,10 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         cp[i].push_back(lp.back());
         max_c = std::max(max_c, (int32_t)cn[i].size());
     }
-    auto lvl = [&](int i) -> const std::vector<int32_t>& { return cp[i]; };
     // a far value is drained and loaded between its chunk and its reader's:
     // K + G + 1 chunks have to fit (K = 1 drains every chunk)
     auto fits = [&](int i, int32_t n, int32_t c) {
-        const std::vector<int32_t>& lp = lvl(i);
+        const std::vector<int32_t>& lp = cp[i];
         const int32_t L = (int32_t)lp.size() - 1;
         for (int32_t l = 0; l < L; l++)
             if (lp[std::min(l + n, L)] - lp[l] > c) return false;
@@ -1017,20 +1026,18 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     }
     const size_t o_bd = tb.add(sizeof(BuildDev) * nd);
     const size_t head_end = tb.off;
-    for (int i = 0; i < nd; i++) o_pos[i] = tb.add(sizeof(int32_t) * N);
-    const size_t pos_end = tb.off;
-    const size_t need_at = tb.add(0);
-    for (int i = 0; i < nd; i++) o_need[i] = tb.add((size_t)N);
-    const size_t need_end = tb.off;
-    const size_t cnt_at = tb.add(0);
+    std::vector<size_t> o_cnt(nd);
+    size_t n_cnt = 0;
     for (int i = 0; i < nd; i++) {
-        o_cnt[i] = tb.off;
-        tb.off += sizeof(int32_t) * (kCand + 2) * cn[i].size();
+        o_cnt[i] = n_cnt;
+        n_cnt += (kCand + 2) * cn[i].size();
     }
-    const size_t cnt_bytes = tb.off - cnt_at;
     struct Temp {
-        char* p = nullptr;
-        ~Temp() { if (p) (void)hipFree(p); }
+        DevBlocks mem;
+        char* head = nullptr;
+        int32_t *pos = nullptr, *cnt = nullptr;   // pos [nd][N]
+        uint8_t* need = nullptr;                  // [nd][N]
+        ~Temp() { mem.release(); }
     } temp;
     std::unique_ptr<RingPlan, void (*)(RingPlan*)> r(new RingPlan(), ring_free);
     // no window walk where its tables and inputs do not fit; other errors are reported
@@ -1039,11 +1046,10 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         set_error("window tables of the batch failed: %s", hipGetErrorString(err));
         return FM_EHIP;
     };
-    hipError_t e = hipMalloc((void**)&temp.p, tb.off + 256);
-    if (e != hipSuccess) { temp.p = nullptr; return give_up(e); }
-    char* const tmp = temp.p;
-    e = hipMemset(tmp + o_pos[0], 0xff, pos_end - o_pos[0]);
-    if (e == hipSuccess) e = hipMemset(tmp + need_at, 0, need_end - need_at);
+    hipError_t e = temp.mem.take({{(void**)&temp.head, head_end}, {(void**)&temp.pos, sizeof(int32_t) * N * nd},
+                                  {(void**)&temp.need, (size_t)N * nd}, {(void**)&temp.cnt, sizeof(int32_t) * n_cnt}});
+    if (e != hipSuccess) return give_up(e);
+    char* const tmp = temp.head;
     for (int i = 0; i < nd; i++) {
         const SrcDev& d = src[i / 2];
         const bool fwd = i % 2 == 0;
@@ -1059,9 +1065,9 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         x.rcv_node = d.rcv_node;
         x.n_rcv_node = fwd ? d.n_ent : 0;
         x.L = (int32_t)cn[i].size();
-        x.pos = (int32_t*)(tmp + o_pos[i]);
-        x.need = (uint8_t*)(tmp + o_need[i]);
-        x.cnt = (int32_t*)(tmp + o_cnt[i]);
+        x.pos = temp.pos + (size_t)i * N;
+        x.need = temp.need + (size_t)i * N;
+        x.cnt = temp.cnt + o_cnt[i];
     }
     BuildArgs ba{};
     ba.dev = (const BuildDev*)(tmp + o_bd);
@@ -1077,18 +1083,19 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
             memcpy(head.data() + o_cl[i], cl[i].data(), sizeof(int32_t) * cl[i].size());
         }
         memcpy(head.data() + o_bd, bd.data(), sizeof(BuildDev) * nd);
-        if (e == hipSuccess) e = hipMemcpy(tmp, head.data(), head_end, hipMemcpyHostToDevice);
+        e = hipMemcpy(tmp, head.data(), head_end, hipMemcpyHostToDevice);
     }
     if (e != hipSuccess) return give_up(e);
     const int gx = (int)std::min<int64_t>((N + 255) / 256, 4096);
+    hipLaunchKernelGGL(k_ring_clear, dim3(gx, nd), dim3(256), 0, nullptr, ba);
     hipLaunchKernelGGL(k_ring_pos, dim3(gx, nd), dim3(256), 0, nullptr, ba);
     hipLaunchKernelGGL(k_ring_count, dim3(max_c, nd), dim3(256), 0, nullptr, ba);
-    std::vector<int32_t> cnt(cnt_bytes / sizeof(int32_t));
+    std::vector<int32_t> cnt(n_cnt);
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpy(cnt.data(), tmp + cnt_at, cnt_bytes, hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(cnt.data(), temp.cnt, sizeof(int32_t) * n_cnt, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return give_up(e);
     auto count = [&](int i, int32_t l, int c) {
-        return cnt[(o_cnt[i] - cnt_at) / sizeof(int32_t) + (size_t)l * (kCand + 2) + c];
+        return cnt[o_cnt[i] + (size_t)l * (kCand + 2) + c];
     };
     // Per direction the smallest side window that holds the entries of any two
     // consecutive chunks, taken where few enough neighbours are far: a far value
@@ -1144,7 +1151,7 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     for (int i = 0; i < nd; i++) {
         if (!bd[i].C) continue;
         const Packed& pk = b->states[i / 2]->pk;
-        const std::vector<int32_t>&lp = lvl(i), &ns = cn[i];
+        const std::vector<int32_t>&lp = cp[i], &ns = cn[i];
         const std::vector<int32_t>& bptr = i % 2 == 0 ? pk.fblk_ptr : pk.rblk_ptr;
         const std::vector<int32_t>& bid = i % 2 == 0 ? pk.fblk_id : pk.rblk_id;
         const std::vector<int32_t>& bpos = i % 2 == 0 ? pk.blk_fpos : pk.blk_rpos;
@@ -1206,8 +1213,8 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         }
     }
     Bytes pb;
-    const size_t o_dev = pb.add(sizeof(RingDev) * nd);
-    std::vector<size_t> o_nd(nd), o_wd(nd), o_fd(nd), o_lv(nd), o_bw(nd), o_ref(nd), o_node(nd), o_wa(nd), o_wb(nd), o_wc(nd), o_wref(nd), o_wwt(nd), o_far(nd), o_lev(nd);
+    const size_t o_dev = pb.add(sizeof(RingDev) * nd), o_build = pb.add(sizeof(BuildDev) * nd);
+    std::vector<size_t> o_nd(nd), o_wd(nd), o_fd(nd), o_lv(nd), o_bw(nd), o_lev(nd);
     for (int i = 0; i < nd; i++) {
         if (!bd[i].C) continue;
         o_nd[i] = pb.add(sizeof(uint2) * ndl[i].size());
@@ -1218,32 +1225,37 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         o_lev[i] = pb.add(sizeof(int32_t) * cl[i].size());
     }
     const size_t host_end = pb.add(0);
+    // one array per stream over all sources (every source on a 256-byte boundary)
+    Bytes st_ref, st_node, st_wa, st_wb, st_wc, st_wref, st_wwt, st_far;
+    std::vector<size_t> o_ref(nd), o_node(nd), o_wa(nd), o_wb(nd), o_wc(nd), o_wref(nd), o_wwt(nd), o_far(nd);
     for (int i = 0; i < nd; i++) {
         if (!bd[i].C) continue;
-        o_ref[i] = pb.add((size_t)N * 8);
-        o_node[i] = pb.add((size_t)N * 4);
-        o_wa[i] = pb.add((size_t)N * 16);
-        o_wb[i] = pb.add(fp64 ? (size_t)N * 8 : 0);
-        o_wc[i] = pb.add(fp64 && i % 2 ? (size_t)N * 8 : 0);
-        o_wref[i] = pb.add((size_t)(n_wide[i] + 1) * 16);
-        o_wwt[i] = pb.add((size_t)(n_wide[i] + 1) * 8 * vb);
+        o_ref[i] = st_ref.add((size_t)N * 8);
+        o_node[i] = st_node.add((size_t)N * 4);
+        o_wa[i] = st_wa.add((size_t)N * 16);
+        o_wb[i] = st_wb.add(fp64 ? (size_t)N * 8 : 0);
+        o_wc[i] = st_wc.add(fp64 && i % 2 ? (size_t)N * 8 : 0);
+        o_wref[i] = st_wref.add((size_t)(n_wide[i] + 1) * 16);
+        o_wwt[i] = st_wwt.add((size_t)(n_wide[i] + 1) * 8 * vb);
+        o_far[i] = st_far.add((size_t)(n_far[i] + 1) * 4);
     }
-    const size_t far_at = pb.add(0);
-    for (int i = 0; i < nd; i++)
-        if (bd[i].C) o_far[i] = pb.add((size_t)(n_far[i] + 1) * 4);
-    const size_t far_end = pb.off;
     // at most a quarter of the free memory: a program that sized its own arrays
     // by a batch's scratch rows keeps its room
     const size_t q_bytes = std::max((size_t)S * N * B, (size_t)S * n_ent * B) * vb + 256;
+    char *tab = nullptr, *ref = nullptr, *node = nullptr, *wa = nullptr, *wb = nullptr, *wc = nullptr, *wref = nullptr,
+         *wwt = nullptr, *far = nullptr;
+    const std::vector<Part> parts = {{(void**)&tab, host_end}, {(void**)&ref, st_ref.off}, {(void**)&node, st_node.off},
+                                     {(void**)&wa, st_wa.off}, {(void**)&wb, st_wb.off}, {(void**)&wc, st_wc.off},
+                                     {(void**)&wref, st_wref.off}, {(void**)&wwt, st_wwt.off},
+                                     {(void**)&far, st_far.off}, {&r->q, q_bytes}};
+    size_t all = 0;
+    for (const Part& x : parts) all += x.bytes;
     size_t mem_free = 0, mem_total = 0;
     e = hipMemGetInfo(&mem_free, &mem_total);
-    if (e != hipSuccess || pb.off + q_bytes > mem_free / 4) return give_up(e);
-    e = hipMalloc(&r->blob, pb.off + 256);
-    if (e != hipSuccess) { r->blob = nullptr; return give_up(e); }
-    e = hipMalloc(&r->q, q_bytes);
-    if (e != hipSuccess) { r->q = nullptr; return give_up(e); }
-    char* pbase = (char*)r->blob;
-    r->dev = (RingDev*)(pbase + o_dev);
+    if (e != hipSuccess || all > mem_free / 4) return give_up(e);
+    e = r->mem.take(parts);
+    if (e != hipSuccess) return give_up(e);
+    r->dev = (RingDev*)(tab + o_dev);
     std::vector<char> hb(host_end);
     std::vector<RingDev> rd(nd);
     for (int i = 0; i < nd; i++) {
@@ -1254,38 +1266,37 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         memcpy(hb.data() + o_lv[i], lv[i].data(), sizeof(int4) * lv[i].size());
         memcpy(hb.data() + o_bw[i], bw[i].data(), sizeof(int32_t) * bw[i].size());
         memcpy(hb.data() + o_lev[i], cl[i].data(), sizeof(int32_t) * cl[i].size());
-        rd[i].ref = (const uint2*)(pbase + o_ref[i]);
-        rd[i].node = (const uint32_t*)(pbase + o_node[i]);
-        rd[i].wa = pbase + o_wa[i];
-        rd[i].wb = pbase + o_wb[i];
-        rd[i].wc = pbase + o_wc[i];
-        rd[i].wref = (const uint32_t*)(pbase + o_wref[i]);
-        rd[i].wwt = pbase + o_wwt[i];
-        rd[i].nd = (const uint2*)(pbase + o_nd[i]);
-        rd[i].wd = (const uint4*)(pbase + o_wd[i]);
-        rd[i].fd = (const uint4*)(pbase + o_fd[i]);
-        rd[i].far = (const uint32_t*)(pbase + o_far[i]);
-        rd[i].blk_w = (const int32_t*)(pbase + o_bw[i]);
+        rd[i].ref = (const uint2*)(ref + o_ref[i]);
+        rd[i].node = (const uint32_t*)(node + o_node[i]);
+        rd[i].wa = wa + o_wa[i];
+        rd[i].wb = wb + o_wb[i];
+        rd[i].wc = wc + o_wc[i];
+        rd[i].wref = (const uint32_t*)(wref + o_wref[i]);
+        rd[i].wwt = wwt + o_wwt[i];
+        rd[i].nd = (const uint2*)(tab + o_nd[i]);
+        rd[i].wd = (const uint4*)(tab + o_wd[i]);
+        rd[i].fd = (const uint4*)(tab + o_fd[i]);
+        rd[i].far = (const uint32_t*)(far + o_far[i]);
+        rd[i].blk_w = (const int32_t*)(tab + o_bw[i]);
         rd[i].n_nd = (int32_t)ndl[i].size() - 2 * kPad;
         rd[i].n_wd = (int32_t)wdl[i].size() - 2 * kPad;
         rd[i].n_fd = (int32_t)fdl[i].size() - 2 * kPad - sh.e;
-        rd[i].lev = (const int32_t*)(pbase + o_lev[i]);
-        bd[i].ref = (uint2*)(pbase + o_ref[i]);
-        bd[i].node = (uint32_t*)(pbase + o_node[i]);
-        bd[i].wa = pbase + o_wa[i];
-        bd[i].wb = fp64 ? pbase + o_wb[i] : nullptr;
-        bd[i].wc = fp64 && i % 2 ? pbase + o_wc[i] : nullptr;
-        bd[i].wref = (uint32_t*)(pbase + o_wref[i]);
-        bd[i].wwt = pbase + o_wwt[i];
-        bd[i].far = (uint32_t*)(pbase + o_far[i]);
-        bd[i].lv = (const int4*)(pbase + o_lv[i]);
+        rd[i].lev = (const int32_t*)(tab + o_lev[i]);
+        bd[i].ref = (uint2*)(ref + o_ref[i]);
+        bd[i].node = (uint32_t*)(node + o_node[i]);
+        bd[i].wa = wa + o_wa[i];
+        bd[i].wb = fp64 ? wb + o_wb[i] : nullptr;
+        bd[i].wc = fp64 && i % 2 ? wc + o_wc[i] : nullptr;
+        bd[i].wref = (uint32_t*)(wref + o_wref[i]);
+        bd[i].wwt = wwt + o_wwt[i];
+        bd[i].far = (uint32_t*)(far + o_far[i]);
+        bd[i].lv = (const int4*)(tab + o_lv[i]);
     }
     memcpy(hb.data() + o_dev, rd.data(), sizeof(RingDev) * nd);
-    // one entry past each far list is loaded by lanes without an entry
-    e = hipMemset(pbase + far_at, 0, far_end - far_at);
-    if (e == hipSuccess) e = hipMemcpy(pbase, hb.data(), host_end, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(tmp + o_bd, bd.data(), sizeof(BuildDev) * nd, hipMemcpyHostToDevice);
+    memcpy(hb.data() + o_build, bd.data(), sizeof(BuildDev) * nd);
+    e = hipMemcpy(tab, hb.data(), host_end, hipMemcpyHostToDevice);
     if (e != hipSuccess) return give_up(e);
+    ba.dev = (const BuildDev*)(tab + o_build);
     hipLaunchKernelGGL(k_ring_mark, dim3(max_c, nd), dim3(256), 0, nullptr, ba);
     if (fp64) hipLaunchKernelGGL(k_ring_fill<double>, dim3(max_c, nd), dim3(256), 0, nullptr, ba);
     else hipLaunchKernelGGL(k_ring_fill<float>, dim3(max_c, nd), dim3(256), 0, nullptr, ba);
