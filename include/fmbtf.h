@@ -355,9 +355,29 @@ int fm_autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision
 /* Change the stream later applies are enqueued on. */
 int fm_batch_set_stream(fm_batch* b, void* hip_stream);
 
-/* The schedule the batch resolved (defaults filled in; with the LDS window walk
- * the schedule its comparison baselines would take). */
+/*
+ * The schedule the batch resolved, defaults filled in: the one of the node split
+ * or the rhs groups, also where the LDS window walk runs in its place
+ * (fm_batch_walk says which kernel runs).  unroll is the primal's: the default
+ * of the node split with 8 lanes per node takes fewer nodes per thread in the
+ * transpose, which no explicit field asks for, and neither does any ask for the
+ * window walk, so that only a schedule of zeros gives both again.
+ */
 int fm_batch_tuning(const fm_batch* b, fm_tuning* out);
+
+/* The kernel that the applies of one direction run. */
+enum { FM_WALK_GROUPS = 0, FM_WALK_SPLIT = 1, FM_WALK_WINDOW = 2 };
+typedef struct fm_walk {
+    int32_t kernel;     /* FM_WALK_GROUPS (rhs groups), FM_WALK_SPLIT (node split), FM_WALK_WINDOW
+                           (LDS window walk) */
+    int32_t threads;    /* workgroup size */
+    int32_t unroll;     /* nodes per thread in flight (0 in the window walk) */
+    int32_t window;     /* window walk: recent values that a workgroup keeps in LDS, else 0 */
+    int32_t side;       /* window walk: slots for values outside the window, else 0 */
+} fm_walk;
+
+/* transpose: 0 for fm_apply_J, 1 for fm_apply_JT.  Errors: FM_EINVAL. */
+int fm_batch_walk(const fm_batch* b, int32_t transpose, fm_walk* out);
 
 /*
  * Wait for the batch stream and report whether the applies enqueued since

@@ -26,7 +26,7 @@ SYMBOLS = (
     "fm_build_frozen_state_pt", "fm_build_frozen_states_pt", "fm_build_frozen_states_gpu",
     "fm_set_iterative_block_min", "fm_state_stats",
     "fm_state_export_operator", "fm_state_export_graph", "fm_state_free",
-    "fm_batch_create", "fm_batch_set_stream", "fm_batch_tuning", "fm_batch_status", "fm_batch_split_info",
+    "fm_batch_create", "fm_batch_set_stream", "fm_batch_tuning", "fm_batch_walk", "fm_batch_status", "fm_batch_split_info",
     "fm_apply_J", "fm_apply_J_static",
     "fm_apply_JT", "fm_apply_J_sweep", "fm_apply_JT_sweep", "fm_batch_free", "fm_last_error",
     "fm_lsqr_create", "fm_lsqr_start", "fm_lsqr_iterate", "fm_lsqr_capture", "fm_lsqr_replay",
@@ -65,6 +65,11 @@ class fm_tuning(C.Structure):
     _fields_ = [("rhs_per_group", C.c_int32), ("threads", C.c_int32),
                 ("min_lds_bytes", C.c_int32), ("xcd_aware", C.c_int32), ("unroll", C.c_int32),
                 ("split", C.c_int32), ("balance", C.c_int32)]
+
+
+class fm_walk(C.Structure):
+    _fields_ = [("kernel", C.c_int32), ("threads", C.c_int32), ("unroll", C.c_int32),
+                ("window", C.c_int32), ("side", C.c_int32)]
 
 
 _lib = None
@@ -108,6 +113,7 @@ def load():
         "fm_autotune": (C.c_int, [vp, i32, i32, i32, vp, vp, i32, vp, i32, vp, i32, vp, i32, i32, C.c_char_p, vp,
                                   vp, vp, i32, vp]),
         "fm_batch_tuning": (C.c_int, [vp, vp]),
+        "fm_batch_walk": (C.c_int, [vp, i32, vp]),
         "fm_batch_status": (C.c_int, [vp]),
         "fm_batch_split_info": (C.c_int, [vp, vp]),
         "fm_apply_J": (C.c_int, [vp, vp, i32, vp, i32]),
@@ -484,6 +490,14 @@ class Batch:
         t = fm_tuning()
         _check(load().fm_batch_tuning(self._ptr, C.byref(t)))
         return {k: getattr(t, k) for k, _ in fm_tuning._fields_}
+
+    def walk(self, transpose=False) -> dict:
+        """The kernel that apply_J (or apply_JT) runs: "groups", "split" or "window"."""
+        w = fm_walk()
+        _check(load().fm_batch_walk(self._ptr, int(bool(transpose)), C.byref(w)))
+        res = {k: getattr(w, k) for k, _ in fm_walk._fields_}
+        res["kernel"] = ("groups", "split", "window")[w.kernel]
+        return res
 
     def status(self):
         """Synchronise the batch stream; raises FmError if a node-split wait timed out."""

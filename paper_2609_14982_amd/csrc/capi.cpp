@@ -30,6 +30,7 @@ int apply_J(fm_batch* b, const void* ds, int32_t ds_mode, void* out, int32_t out
 int apply_JT(fm_batch* b, const void* w, int32_t w_mode, void* out, int32_t out_mode);
 int batch_set_stream(fm_batch* b, void* stream);
 int batch_tuning(const fm_batch* b, fm_tuning* out);
+int batch_walk(const fm_batch* b, int32_t transpose, fm_walk* out);
 int batch_status(fm_batch* b);
 int batch_split_info(fm_batch* b, int32_t* xcd_masks);
 int autotune(fm_state* const* states, int32_t S, int32_t B, int32_t precision, void* stream, const void* ds,
@@ -256,6 +257,11 @@ int fm_batch_set_stream(fm_batch* b, void* hip_stream) {
 int fm_batch_tuning(const fm_batch* b, fm_tuning* out) {
     fm::clear_error();
     return fm::batch_tuning(b, out);
+}
+
+int fm_batch_walk(const fm_batch* b, int32_t transpose, fm_walk* out) {
+    fm::clear_error();
+    return fm::batch_walk(b, transpose, out);
 }
 
 int fm_batch_status(fm_batch* b) {

@@ -1857,4 +1857,18 @@ int batch_tuning(const fm_batch* b, fm_tuning* out) {
     return FM_OK;
 }
 
+int batch_walk(const fm_batch* b, int32_t transpose, fm_walk* out) {
+    if (!b || !out) { set_error("null argument"); return FM_EINVAL; }
+    *out = fm_walk{};
+    if (ring_has(b->ring, !transpose)) {
+        out->kernel = FM_WALK_WINDOW;
+        ring_sizes(b->ring, !transpose, &out->threads, &out->window, &out->side);
+        return FM_OK;
+    }
+    out->kernel = b->tun.split > 1 ? FM_WALK_SPLIT : FM_WALK_GROUPS;
+    out->threads = b->tun.threads;
+    out->unroll = b->tun.split > 1 && transpose ? b->split_unroll_rev : b->tun.unroll;
+    return FM_OK;
+}
+
 }  // namespace fm

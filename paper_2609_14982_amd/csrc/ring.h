@@ -16,6 +16,9 @@ void ring_free(RingPlan* r);
 // The walk of that direction is to be taken (r may be nullptr).
 bool ring_has(const RingPlan* r, bool fwd);
 
+// Its workgroup size, window and side slots.
+void ring_sizes(const RingPlan* r, bool fwd, int32_t* threads, int32_t* window, int32_t* side);
+
 // One walk over the batch on its stream: a.work / a.xB / a.in / a.out and the
 // modes as for the other walk kernels.
 hipError_t ring_walk(const fm_batch* b, bool fwd, const ApplyArgs& a);

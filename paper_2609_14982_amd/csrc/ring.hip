@@ -1337,6 +1337,13 @@ static void ring_inputs(const fm_batch* b, bool fwd, const ApplyArgs& a, const R
 
 bool ring_has(const RingPlan* r, bool fwd) { return r && r->C[fwd ? 0 : 1] > 0; }
 
+void ring_sizes(const RingPlan* r, bool fwd, int32_t* threads, int32_t* window, int32_t* side) {
+    const Shape sh = kShapes[r->shape];
+    *threads = (sh.cw + sh.ow + sh.fw) * 64;
+    *window = r->C[fwd ? 0 : 1];
+    *side = r->F[fwd ? 0 : 1];
+}
+
 hipError_t ring_walk(const fm_batch* b, bool fwd, const ApplyArgs& a0) {
     const RingPlan* r = b->ring;
     const bool fp64 = b->prec == FM_FP64;
