@@ -71,6 +71,32 @@ def layout_bytes(stats_list, B, vbytes, wbytes, broadcast_once=False):
     return total
 
 
+def window_bytes(stats_list, B, vbytes):
+    """Bytes per primal apply of the LDS window walk as laid out (input pass and
+    walk): per (source, rhs) and node the input row read and written in level
+    order, then read with its slots, node id and weights (12 + 24 bytes in FP64,
+    12 + 16 in FP32); per source the order and calibration of the input pass and
+    the dense blocks.  Node rows that are stored or read back come on top."""
+    total = 0
+    for st in stats_list:
+        N = st["N"]
+        total += B * N * (3 * vbytes + 12 + (24 if vbytes == 8 else 16)) + (8 + vbytes) * N + \
+            B * (8 * st.get("dense_k2", st["sum_k2"]) + 12 * st.get("iter_nnz", 0))
+    return total
+
+
+def schedule_report(batch):
+    """(kernel of the primal apply, schedule that creates the batch again, with
+    the kernels of both directions).  The window walk and the node split's mixed
+    default come from a schedule of zeros only."""
+    walks = [batch.walk(False), batch.walk(True)]
+    sched = dict(batch.tuning())
+    if any(w["kernel"] == "window" for w in walks) or walks[0]["unroll"] != walks[1]["unroll"]:
+        sched = {k: 0 for k in sched}
+    sched["J"], sched["JT"] = walks
+    return {"window": "k_ring", "split": "k_split", "groups": "k_sweep"}[walks[0]["kernel"]], sched
+
+
 KERNEL_SOURCES = ("paper_2609_14982_amd/csrc/sweep.h", "paper_2609_14982_amd/csrc/split.h",
                   "paper_2609_14982_amd/csrc/device.hip", "paper_2609_14982_amd/csrc/setup.cpp")
 
@@ -367,7 +393,8 @@ def main():
     t1 = time.perf_counter()
     batch = fm.Batch(states, B, prec, tuning=tuning or None, stream=stream)
     torch.cuda.synchronize()
-    log(f"batch create + upload: {time.perf_counter() - t1:.1f}s, tuning {batch.tuning()}")
+    kname, schedule = schedule_report(batch)
+    log(f"batch create + upload: {time.perf_counter() - t1:.1f}s, schedule {schedule}")
 
     # the timed loop: LSQR iterations, each one replay of a captured graph
     lsqr = fm.Lsqr(batch)
@@ -420,7 +447,7 @@ def main():
     # all ran on one XCD exchange their node values through one L2 (the
     # others paid device-scope fences at every level)
     placement = None
-    if batch.tuning()["split"] > 1:
+    if schedule["JT"]["kernel"] == "split":
         xm = batch.split_info()
         one = int(sum(1 for m in xm if bin(int(m) & 0xFFFFFFFF).count("1") == 1))
         placement = {"sources_on_one_xcd": one, "sources": int(len(xm))}
@@ -428,9 +455,8 @@ def main():
 
     # roofline of the dominant kernel: the primal sweep (one launch per apply_J,
     # between a counter reset of S words and the receiver gather of S*R*B
-    # values, together <0.1 % of the window)
-    split = batch.tuning()["split"] > 1
-    kname = "k_split" if split else "k_sweep"
+    # values, together <0.1 % of the window; the window walk's input pass is
+    # part of its time)
     bytes_J = algorithmic_bytes(stats, B, vbytes, vbytes)
     gbs_J = bytes_J / (tJ.mean() * 1e-3) / 1e9
     gbs_T = bytes_J / (tT.mean() * 1e-3) / 1e9
@@ -442,8 +468,10 @@ def main():
             "kernel": f"{kname} primal (apply_J)",
             "bytes_per_launch": bytes_J,
             "bytes_model": "per (source, rhs) 2*vbytes*N, per source N*(ebar*(wbytes+4)+4+wbytes+4) + 8*sum k^2",
-            "bytes_layout": layout_bytes(stats, B, vbytes, vbytes),
-            "bytes_layout_broadcast_once": layout_bytes(stats, B, vbytes, vbytes, broadcast_once=True),
+            "bytes_layout": (window_bytes(stats, B, vbytes) if kname == "k_ring"
+                             else layout_bytes(stats, B, vbytes, vbytes)),
+            "bytes_layout_broadcast_once": (None if kname == "k_ring" else
+                                            layout_bytes(stats, B, vbytes, vbytes, broadcast_once=True)),
             "launch_ms": round(float(tJ.mean()), 4), "launch_ms_median": round(float(np.median(tJ)), 4),
             "launches_timed": reps,
             "placement": placement,
@@ -541,7 +569,7 @@ def main():
                                f"{S} sources x {B} rhs, {R} receivers"
                                + (", 26-neighbour cube stencil" if args.stencil == 26 else ""),
                    "stencil": args.stencil,
-                   "schedule": batch.tuning(),
+                   "schedule": schedule,
                    "schedule_cached": tune_cached,
                    "schedule_search": ([{"split": t["split"], "threads": t["threads"], "unroll": t["unroll"],
                                          "balance": t.get("balance", 0), "min_lds_bytes": t["min_lds_bytes"],
