@@ -60,7 +60,7 @@ constexpr uint32_t kCntMask = 1023u, kLast = 1u << 10, kBlk = 1u << 11, kDrain =
 constexpr uint32_t kStore = 1u << 31;      // ref word 0: the node row is read again from memory
 constexpr uint32_t kRcvEntry = 1u << 31;   // far-list entry: receiver input instead of a node row
 
-// One direction of one source.  Slots of the window (RG values each):
+// One direction of one source.  Slots of the window (a value each):
 // [0, C) position p at p mod C, C a zero, then F side slots.
 struct RingDev {
     const uint2* ref;         // [N] slots 0 and 1, slot 2 and the input's slot
@@ -83,7 +83,7 @@ struct RingDev {
 
 struct RingArgs {
     const RingDev* dev;       // [S][2]
-    const void* q;            // [S][groups][N][RG] inputs in level order, or receiver inputs [S][n_ent][B]
+    const void* q;            // [S][B][N] inputs in level order, or receiver inputs [S][n_ent][B]
     int32_t C, F;
     int32_t stage_off;        // first byte of the block staging area in LDS
     int32_t store_all;        // every node row is an output
@@ -134,7 +134,7 @@ __device__ __forceinline__ const T* uptr(const T* p) {
 
 template <typename V>
 struct WalkCtx {
-    V* X;                     // node rows of this source, at this group's first value
+    V* X;                     // node rows of this source, at this right-hand side
     V* outp;                  // per-source output rows of the transpose, or nullptr
     uint32_t xB, oB;          // values per row
     bool store_all;
@@ -144,7 +144,7 @@ struct WalkCtx {
     const SrcDev* sd;
     const RingDev* rd;
     const void* q;            // this item's inputs in level order, or nullptr
-    const V* in;              // primal: rows of ds, at this group's first value
+    const V* in;              // primal: rows of ds, at this right-hand side
     uint32_t lds;             // LDS address of the window
     int stage_off;
 };
@@ -154,46 +154,27 @@ struct WalkCtx {
 // columns of a block are split over groups of whole waves when it has fewer
 // rows than the workgroup has threads, and the partial sums added in column
 // order.
-template <int DIR, typename V, int RG, int TB, bool QS>
+template <int DIR, typename V, int TB, bool QS>
 __device__ __forceinline__ void ring_blocks(const WalkCtx<V>& w) {
-    typedef Pack<V, RG> P;
-    typedef __attribute__((address_space(3))) P lds_p;
+    typedef __attribute__((address_space(3))) V lds_v;
     typedef __attribute__((address_space(3))) double lds_d;
-    lds_p* win = (lds_p*)w.lds;
-    lds_d* sb = (lds_d*)(w.lds + (uint32_t)w.stage_off);
-    auto rd_win = [&](uint32_t s) {
-        P x;
-        typedef __attribute__((address_space(3))) const V lds_v;
-        lds_v* v = (lds_v*)(win + s);
-#pragma unroll
-        for (int i = 0; i < RG; ++i) x.v[i] = v[i];
-        return x;
-    };
+    lds_v* win = (lds_v*)(uintptr_t)w.lds;
+    lds_d* sb = (lds_d*)(uintptr_t)(w.lds + (uint32_t)w.stage_off);
     const SrcDev& sd = *w.sd;
     const RingDev& rd = *w.rd;
-    const P* q = (const P*)w.q;
+    const V* q = (const V*)w.q;
     const int tid = (int)threadIdx.x;
     const int lev = gld(rd.lev + w.l);
     const int b0 = gld((DIR == kFwd ? sd.fblk_ptr : sd.rblk_ptr) + lev);
     const int b1 = gld((DIR == kFwd ? sd.fblk_ptr : sd.rblk_ptr) + lev + 1);
     const V* __restrict__ wwt = (const V*)rd.wwt;
     // member i's result: window slot, node row, per-source output
-    auto put_member = [&](int w0, int i, int bp, const double acc[RG]) {
+    auto put_member = [&](int w0, int i, int bp, double acc) {
         const uint32_t node = gld(rd.wref + (size_t)(w0 + i) * 4) & ~kStore;
-        P o;
-        __attribute__((address_space(3))) V* dst = (__attribute__((address_space(3))) V*)(win + (bp + i) % w.C);
-#pragma unroll
-        for (int v = 0; v < RG; ++v) {
-            o.v[v] = (V)acc[v];
-            dst[v] = o.v[v];
-        }
-        st<V, RG>(w.X + (size_t)node * w.xB, o);
-        if (DIR == kRev && w.outp) {
-            const V c = gld(wwt + (size_t)(w0 + i) * 8);
-#pragma unroll
-            for (int v = 0; v < RG; ++v) o.v[v] = c * o.v[v];
-            st<V, RG>(w.outp + (size_t)node * w.oB, o);
-        }
+        const V o = (V)acc;
+        win[(bp + i) % w.C] = o;
+        w.X[(size_t)node * w.xB] = o;
+        if (DIR == kRev && w.outp) w.outp[(size_t)node * w.oB] = gld(wwt + (size_t)(w0 + i) * 8) * o;
     };
     for (int bi = b0; bi < b1; ++bi) {
         const int blk = gld((DIR == kFwd ? sd.fblk_id : sd.rblk_id) + bi);
@@ -203,28 +184,18 @@ __device__ __forceinline__ void ring_blocks(const WalkCtx<V>& w) {
         for (int m = tid; m < k; m += TB) {
             const uint32_t* rf = rd.wref + (size_t)(w0 + m) * 4;
             const V* wt = wwt + (size_t)(w0 + m) * 8;
-            double acc[RG];
-            if constexpr (DIR == kFwd && sizeof(V) == 4) {
+            double acc;
+            if constexpr (DIR == kFwd && sizeof(V) == 4)
                 // (c ds is exact in FP64; the input pass has rounded it to FP32)
-                const V* ds = w.in + (size_t)(gld(rf) & ~kStore) * w.oB;
-                const double c = (double)gld(wt);
-#pragma unroll
-                for (int v = 0; v < RG; ++v) acc[v] = c * (double)gld(ds + v);
-            } else {
-                const P r = QS ? rd_win(gld(reinterpret_cast<const uint32_t*>(wt + 7))) : glv(q + bp + m);
-#pragma unroll
-                for (int v = 0; v < RG; ++v) acc[v] = (double)r.v[v];
-            }
+                acc = (double)gld(wt) * (double)gld(w.in + (size_t)(gld(rf) & ~kStore) * w.oB);
+            else
+                acc = (double)(QS ? win[gld(reinterpret_cast<const uint32_t*>(wt + 7))] : gld(q + bp + m));
 #pragma unroll
             for (int t = 0; t < 6; ++t) {
                 const uint32_t s = (gld(rf + 1 + t / 2) >> (16 * (t & 1))) & 0xffffu;
-                const double wv = (double)gld(wt + 1 + t);
-                const P x = rd_win(s);
-#pragma unroll
-                for (int v = 0; v < RG; ++v) acc[v] += wv * (double)x.v[v];
+                acc += (double)gld(wt + 1 + t) * (double)win[s];
             }
-#pragma unroll
-            for (int v = 0; v < RG; ++v) sb[m * RG + v] = acc[v];
+            sb[m] = acc;
         }
         wg_barrier();
         const int m_it = gld(sd.blk_it + 2 * blk + (DIR == kFwd ? 0 : 1));
@@ -237,25 +208,14 @@ __device__ __forceinline__ void ring_blocks(const WalkCtx<V>& w) {
             const int32_t* __restrict__ cl = DIR == kFwd ? sd.sp_col : sd.spt_col;
             const double* __restrict__ wv = DIR == kFwd ? sd.sp_w : sd.spt_w;
             for (int j = 1; j <= m_it; ++j) {
-                lds_d* cur = j == 1 ? sb : sb + k * RG * (1 + ((j - 1) & 1));
-                lds_d* nxt = sb + k * RG * (1 + (j & 1));
+                lds_d* cur = j == 1 ? sb : sb + k * (1 + ((j - 1) & 1));
+                lds_d* nxt = sb + k * (1 + (j & 1));
                 for (int i = tid; i < k; i += TB) {
-                    double acc[RG];
-#pragma unroll
-                    for (int v = 0; v < RG; ++v) acc[v] = sb[i * RG + v];
+                    double acc = sb[i];
                     const int e1 = gld(rp + i + 1);
-                    for (int e = gld(rp + i); e < e1; ++e) {
-                        const double c = gld(wv + e);
-                        const int col = gld(cl + e);
-#pragma unroll
-                        for (int v = 0; v < RG; ++v) acc[v] += c * cur[col * RG + v];
-                    }
-                    if (j < m_it) {
-#pragma unroll
-                        for (int v = 0; v < RG; ++v) nxt[i * RG + v] = acc[v];
-                    } else {
-                        put_member(w0, i, bp, acc);
-                    }
+                    for (int e = gld(rp + i); e < e1; ++e) acc += gld(wv + e) * cur[gld(cl + e)];
+                    if (j < m_it) nxt[i] = acc;
+                    else put_member(w0, i, bp, acc);
                 }
                 wg_barrier();
             }
@@ -263,16 +223,14 @@ __device__ __forceinline__ void ring_blocks(const WalkCtx<V>& w) {
         }
         const int kw = (k + 63) & ~63;
         const int parts = kw < TB ? TB / kw : 1;
-        lds_d* part = sb + k * RG;        // [parts - 1][kw][RG]
+        lds_d* part = sb + k;             // [parts - 1][kw]
         const __attribute__((address_space(1))) double* __restrict__ Mx =
             gptr((DIR == kFwd ? sd.inv : sd.invt) + gld(sd.blk_inv + blk));
         for (int r0 = 0; r0 < k; r0 += TB) {
             const int pt = parts > 1 ? tid / kw : 0;
             const int i = parts > 1 ? tid - pt * kw : r0 + tid;
             const bool own = i < k && pt < parts;
-            double acc[RG];
-#pragma unroll
-            for (int v = 0; v < RG; ++v) acc[v] = 0.0;
+            double acc = 0.0;
             if (own) {
                 const int j1 = (int)((int64_t)k * (pt + 1) / parts);
                 int j = (int)((int64_t)k * pt / parts);
@@ -282,24 +240,14 @@ __device__ __forceinline__ void ring_blocks(const WalkCtx<V>& w) {
 #pragma unroll
                     for (int t = 0; t < G; ++t) m[t] = Mx[(size_t)(j + t) * k + i];
 #pragma unroll
-                    for (int t = 0; t < G; ++t)
-#pragma unroll
-                        for (int v = 0; v < RG; ++v) acc[v] += m[t] * sb[(j + t) * RG + v];
+                    for (int t = 0; t < G; ++t) acc += m[t] * sb[j + t];
                 }
-                for (; j < j1; ++j) {
-                    const double m = Mx[(size_t)j * k + i];
-#pragma unroll
-                    for (int v = 0; v < RG; ++v) acc[v] += m * sb[j * RG + v];
-                }
-                if (pt > 0)
-#pragma unroll
-                    for (int v = 0; v < RG; ++v) part[((pt - 1) * kw + i) * RG + v] = acc[v];
+                for (; j < j1; ++j) acc += Mx[(size_t)j * k + i] * sb[j];
+                if (pt > 0) part[(pt - 1) * kw + i] = acc;
             }
             if (parts > 1) wg_barrier();
             if (own && pt == 0) {
-                for (int p = 0; p + 1 < parts; ++p)
-#pragma unroll
-                    for (int v = 0; v < RG; ++v) acc[v] += part[(p * kw + i) * RG + v];
+                for (int p = 0; p + 1 < parts; ++p) acc += part[p * kw + i];
                 put_member(w0, i, bp, acc);
             }
         }
@@ -321,10 +269,10 @@ __device__ __forceinline__ void level_end(uint32_t flags, WalkCtx<V>& w) {
     ++w.l;
 }
 
-template <int DIR, typename V, int RG, int TB, bool QS>
+template <int DIR, typename V, int TB, bool QS>
 __device__ __forceinline__ void round_end(WalkCtx<V>& w) {
     if (!w.blk) return;
-    ring_blocks<DIR, V, RG, TB, QS>(w);
+    ring_blocks<DIR, V, TB, QS>(w);
     drain();
     wg_barrier();
     ++w.l;
@@ -332,18 +280,13 @@ __device__ __forceinline__ void round_end(WalkCtx<V>& w) {
 }
 
 // A node's result: window slot, node row, per-source output.
-template <bool PS, typename V, int RG>
-__device__ __forceinline__ void put_node(const WalkCtx<V>& w, Pack<V, RG>* win, const Pack<V, RG>& o, uint32_t slot,
-                                         uint32_t ref0, V c) {
+template <bool PS, typename V>
+__device__ __forceinline__ void put_node(const WalkCtx<V>& w, V* win, V o, uint32_t slot, uint32_t ref0, V c) {
     win[slot] = o;
     const uint32_t node = ref0 & ~kStore;
-    if (w.store_all || (ref0 & kStore)) st<V, RG>(reinterpret_cast<V*>(reinterpret_cast<char*>(w.X) + node * (w.xB * (uint32_t)sizeof(V))), o);
-    if (PS) {
-        Pack<V, RG> os;
-#pragma unroll
-        for (int v = 0; v < RG; ++v) os.v[v] = c * o.v[v];
-        st<V, RG>(w.outp + (size_t)node * w.oB, os);
-    }
+    if (w.store_all || (ref0 & kStore))
+        *reinterpret_cast<V*>(reinterpret_cast<char*>(w.X) + node * (w.xB * (uint32_t)sizeof(V))) = o;
+    if (PS) w.outp[(size_t)node * w.oB] = c * o;
 }
 
 // CW waves: nodes with at most three neighbours, one per lane.  Every stream
@@ -352,13 +295,12 @@ __device__ __forceinline__ void put_node(const WalkCtx<V>& w, Pack<V, RG>* win, 
 // cannot hold a line for a second load (records of 32 bytes, two loads per
 // line: 0.95 ms on the 101x101x51 grid against 0.72 ms with half the batches in
 // flight).
-template <int DIR, typename V, int RG, int TB, int D, bool QS, bool PS>
+template <int DIR, typename V, int TB, int D, bool QS, bool PS>
 __device__ __forceinline__ void walk_narrow(const RingDev& rd, WalkCtx<V>& w, char* lds,
-                                            const Pack<V, RG>* __restrict__ q, int lane) {
-    typedef Pack<V, RG> P;
+                                            const V* __restrict__ q, int lane) {
     constexpr bool F64 = sizeof(V) == 8;
     constexpr bool SC = F64 && PS;       // c is a stream of its own
-    P* win = reinterpret_cast<P*>(lds);
+    V* win = reinterpret_cast<V*>(lds);
     const void* __restrict__ wa = uptr(static_cast<const char*>(rd.wa));
     const void* __restrict__ wb = uptr(static_cast<const char*>(rd.wb));
     const void* __restrict__ wc = uptr(static_cast<const char*>(rd.wc));
@@ -370,8 +312,7 @@ __device__ __forceinline__ void walk_narrow(const RingDev& rd, WalkCtx<V>& w, ch
         uint2 rf;
         uint32_t nd, y;
         Pack<V, 16 / sizeof(V)> wa;
-        V wb, wc;
-        P q;
+        V wb, wc, q;
     } s[D];
     uint2 ahead[D];
     // every lane loads a valid position (the batch's last one when it has no
@@ -386,7 +327,7 @@ __device__ __forceinline__ void walk_narrow(const RingDev& rd, WalkCtx<V>& w, ch
         if (F64) t.wb = ldo<V>(wb, p * 8u);
         if (SC) t.wc = ldo<V>(wc, p * 8u);
         t.nd = ldo<uint32_t>(node, p * 4u);
-        if (!QS) t.q = ldo<P>(q, p * (uint32_t)sizeof(P));
+        if (!QS) t.q = ldo<V>(q, p * (uint32_t)sizeof(V));
     };
     // the first two rounds of the loop only load the first batches (loads before
     // it would be in another order, and the memory counter is waited for by
@@ -402,36 +343,30 @@ __device__ __forceinline__ void walk_narrow(const RingDev& rd, WalkCtx<V>& w, ch
         for (int j = 0; j < D; ++j) {
             const uint32_t y = s[j].y;
             if (lane < (int)(y & kCntMask)) {
-                const P x0 = win[s[j].rf.x & 0xffffu], x1 = win[s[j].rf.x >> 16], x2 = win[s[j].rf.y & 0xffffu];
-                P o;
-                if (QS) o = win[s[j].rf.y >> 16];
-                else o = s[j].q;
+                const V x0 = win[s[j].rf.x & 0xffffu], x1 = win[s[j].rf.x >> 16], x2 = win[s[j].rf.y & 0xffffu];
+                V o = QS ? win[s[j].rf.y >> 16] : s[j].q;
                 const V w3 = F64 ? s[j].wb : s[j].wa.v[F64 ? 0 : 2];
                 const V c = F64 ? s[j].wc : s[j].wa.v[F64 ? 0 : 3];
-#pragma unroll
-                for (int v = 0; v < RG; ++v) o.v[v] += s[j].wa.v[0] * x0.v[v];
-#pragma unroll
-                for (int v = 0; v < RG; ++v) o.v[v] += s[j].wa.v[1] * x1.v[v];
-#pragma unroll
-                for (int v = 0; v < RG; ++v) o.v[v] += w3 * x2.v[v];
+                o += s[j].wa.v[0] * x0;
+                o += s[j].wa.v[1] * x1;
+                o += w3 * x2;
                 uint32_t slot = (y >> 16) + (uint32_t)lane;
                 if (slot >= (uint32_t)w.C) slot -= (uint32_t)w.C;
-                put_node<PS, V, RG>(w, win, o, slot, s[j].nd, c);
+                put_node<PS, V>(w, win, o, slot, s[j].nd, c);
             }
             fetch(s[j], ahead[j]);
             ahead[j] = glv(nd + n + j + 2 * D);
             if (y & kLast) level_end(y, w);
         }
-        round_end<DIR, V, RG, TB, QS>(w);
+        round_end<DIR, V, TB, QS>(w);
     }
 }
 
 // OW waves: the level's nodes with four to six neighbours.
-template <int DIR, typename V, int RG, int TB, int D, bool QS, bool PS>
+template <int DIR, typename V, int TB, int D, bool QS, bool PS>
 __device__ __forceinline__ void walk_wide(const RingDev& rd, WalkCtx<V>& w, char* lds,
-                                            const Pack<V, RG>* __restrict__ q, int lane) {
-    typedef Pack<V, RG> P;
-    P* win = reinterpret_cast<P*>(lds);
+                                            const V* __restrict__ q, int lane) {
+    V* win = reinterpret_cast<V*>(lds);
     const V* __restrict__ wwt = uptr((const V*)rd.wwt);
     const uint4* __restrict__ wref = uptr(reinterpret_cast<const uint4*>(rd.wref));
     const uint4* __restrict__ wd = uptr(rd.wd);
@@ -440,7 +375,7 @@ __device__ __forceinline__ void walk_wide(const RingDev& rd, WalkCtx<V>& w, char
         uint32_t y, skip;
         uint4 rf;
         Pack<V, 4> wa, wb;
-        P q;
+        V q;
     } s[D];
     uint4 ahead[D];
     auto fetch = [&](Stage& t, uint4 d) {
@@ -451,7 +386,7 @@ __device__ __forceinline__ void walk_wide(const RingDev& rd, WalkCtx<V>& w, char
         t.rf = ldo<uint4>(wref, (w0 + i) * 16u);
         t.wa = ldo<Pack<V, 4>>(wwt, (w0 + i) * (uint32_t)(8 * sizeof(V)));
         t.wb = ldo<Pack<V, 4>>(wwt, (w0 + i) * (uint32_t)(8 * sizeof(V)) + (uint32_t)(4 * sizeof(V)));
-        if (!QS) t.q = ldo<P>(q, (p0 + i) * (uint32_t)sizeof(P));
+        if (!QS) t.q = ldo<V>(q, (p0 + i) * (uint32_t)sizeof(V));
     };
 #pragma unroll
     for (int j = 0; j < D; ++j) {
@@ -470,10 +405,10 @@ __device__ __forceinline__ void walk_wide(const RingDev& rd, WalkCtx<V>& w, char
                 const uint32_t sl[6] = {s[j].rf.y & 0xffffu, s[j].rf.y >> 16, s[j].rf.z & 0xffffu,
                                         s[j].rf.z >> 16,     s[j].rf.w & 0xffffu, s[j].rf.w >> 16};
                 const V wt[6] = {s[j].wa.v[1], s[j].wa.v[2], s[j].wa.v[3], s[j].wb.v[0], s[j].wb.v[1], s[j].wb.v[2]};
-                P x[6];
+                V x[6];
 #pragma unroll
                 for (int t = 0; t < 6; ++t) x[t] = win[sl[t]];
-                P o;
+                V o;
                 if (QS) {
                     uint32_t qs;
                     const V tag = s[j].wb.v[3];
@@ -483,18 +418,16 @@ __device__ __forceinline__ void walk_wide(const RingDev& rd, WalkCtx<V>& w, char
                     o = s[j].q;
                 }
 #pragma unroll
-                for (int t = 0; t < 6; ++t)
-#pragma unroll
-                    for (int v = 0; v < RG; ++v) o.v[v] += wt[t] * x[t].v[v];
+                for (int t = 0; t < 6; ++t) o += wt[t] * x[t];
                 uint32_t slot = (y >> 16) + (uint32_t)lane;
                 if (slot >= (uint32_t)w.C) slot -= (uint32_t)w.C;
-                put_node<PS, V, RG>(w, win, o, slot, s[j].rf.x, s[j].wa.v[0]);
+                put_node<PS, V>(w, win, o, slot, s[j].rf.x, s[j].wa.v[0]);
             }
             fetch(s[j], ahead[j]);
             ahead[j] = glv(wd + n + j + 2 * D);
             if (y & kLast) level_end(y, w);
         }
-        round_end<DIR, V, RG, TB, QS>(w);
+        round_end<DIR, V, TB, QS>(w);
     }
 }
 
@@ -504,12 +437,11 @@ __device__ __forceinline__ void walk_wide(const RingDev& rd, WalkCtx<V>& w, char
 // before the values and the list's place E before those (static data): each
 // wait is for loads that are as many levels old, a load through the caches
 // taking as long as several narrow levels.
-template <int DIR, typename V, int RG, int TB, int FT, int G, int E, int U, bool QS>
+template <int DIR, typename V, int TB, int FT, int G, int E, int U, bool QS>
 __device__ __forceinline__ void walk_far(const RingDev& rd, WalkCtx<V>& w, char* lds, const V* __restrict__ rv, int B, int F,
                                          int lane) {
     static_assert(E % G == 0 && G < E, "the slots of the values repeat within a round; three rounds fill the pipeline");
-    typedef Pack<V, RG> P;
-    P* win = reinterpret_cast<P*>(lds);
+    V* win = reinterpret_cast<V*>(lds);
     const uint32_t side = (uint32_t)w.C + 1u;
     const uint32_t* __restrict__ far = uptr(rd.far);
     const uint4* __restrict__ fd = uptr(rd.fd);
@@ -517,11 +449,11 @@ __device__ __forceinline__ void walk_far(const RingDev& rd, WalkCtx<V>& w, char*
     auto value = [&](uint32_t e) {
         // (receiver entries have no use where the input is streamed)
         const bool rcv = (e & kRcvEntry) != 0u;
-        if (!QS) return ldo<P>(w.X, (rcv ? 0u : e) * (w.xB * (uint32_t)sizeof(V)));
+        if (!QS) return ldo<V>(w.X, (rcv ? 0u : e) * (w.xB * (uint32_t)sizeof(V)));
         const char* src = rcv ? reinterpret_cast<const char*>(rv) : reinterpret_cast<const char*>(w.X);
-        return ldo<P>(src, (e & ~kRcvEntry) * ((rcv ? (uint32_t)B : w.xB) * (uint32_t)sizeof(V)));
+        return ldo<V>(src, (e & ~kRcvEntry) * ((rcv ? (uint32_t)B : w.xB) * (uint32_t)sizeof(V)));
     };
-    auto put = [&](const uint4& d, int i, const P& x) {
+    auto put = [&](const uint4& d, int i, V x) {
         uint32_t s = d.w + (uint32_t)i;
         if (s >= (uint32_t)F) s -= (uint32_t)F;
         win[side + s] = x;
@@ -532,7 +464,7 @@ __device__ __forceinline__ void walk_far(const RingDev& rd, WalkCtx<V>& w, char*
     };
     auto whole = [&](const uint4& d) { return uint4{uni(d.x), uni(d.y), uni(d.z), uni(d.w)}; };
     uint4 dv[G], de[E], dd[E];
-    P val[G][U];
+    V val[G][U];
     uint32_t ent[E][U];
     // a lane without an entry loads the last one (every step is the same
     // number of loads)
@@ -570,39 +502,33 @@ __device__ __forceinline__ void walk_far(const RingDev& rd, WalkCtx<V>& w, char*
             if (flags & kLast) level_end(flags, w);
             flags = d.z;
         }
-        round_end<DIR, V, RG, TB, QS>(w);
+        round_end<DIR, V, TB, QS>(w);
     }
 }
 
 // QS: the input is at a side slot (transpose from receiver data); otherwise
 // it is streamed in level order.  PS: c lambda is written per source.
-template <int DIR, typename V, int RG, int CW, int OW, int FW, int D, int DW, int G, int E, int U, bool QS, bool PS>
+template <int DIR, typename V, int CW, int OW, int FW, int D, int DW, int G, int E, int U, bool QS, bool PS>
 __global__ __launch_bounds__((CW + OW + FW) * 64) void k_ring(ApplyArgs a, RingArgs r) {
     constexpr int TB = (CW + OW + FW) * 64;
-    typedef Pack<V, RG> P;
     const int wg = blockIdx.x;
     const int item = (wg % 8) * a.per_xcd + (wg / 8);
     if (item >= a.items) return;
-    const int alpha = item / a.ngroups;
-    const int grp = item - alpha * a.ngroups;
+    const int alpha = item / a.B, rhs = item - alpha * a.B;
     extern __shared__ char ring_lds[];
     WalkCtx<V> w;
-    const int rhs0 = grp * RG;
-    w.X = (V*)a.work + (size_t)alpha * a.N * a.xB + rhs0;
-    w.outp = DIR == kRev && a.out_mode == FM_JT_PER_SOURCE ? (V*)a.out + (size_t)alpha * a.N * a.B + rhs0 : nullptr;
+    w.X = (V*)a.work + (size_t)alpha * a.N * a.xB + rhs;
+    w.outp = DIR == kRev && a.out_mode == FM_JT_PER_SOURCE ? (V*)a.out + (size_t)alpha * a.N * a.B + rhs : nullptr;
     w.xB = (uint32_t)a.xB;
     w.oB = (uint32_t)a.B;
     w.store_all = r.store_all != 0;
     w.C = r.C;
     w.l = 0;
     w.blk = false;
-    const P* q = QS ? nullptr : (const P*)r.q + (size_t)item * a.N;
-    const V* rv = QS ? (const V*)r.q + (size_t)alpha * r.n_ent * a.B + rhs0 : nullptr;
+    const V* q = QS ? nullptr : (const V*)r.q + (size_t)item * a.N;
+    const V* rv = QS ? (const V*)r.q + (size_t)alpha * r.n_ent * a.B + rhs : nullptr;
     if (threadIdx.x == 0) {
-        P z;
-#pragma unroll
-        for (int v = 0; v < RG; ++v) z.v[v] = (V)0;
-        reinterpret_cast<P*>(ring_lds)[r.C] = z;
+        reinterpret_cast<V*>(ring_lds)[r.C] = (V)0;
         if (r.xmask) {
             unsigned x;
             asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(x));
@@ -613,16 +539,16 @@ __global__ __launch_bounds__((CW + OW + FW) * 64) void k_ring(ApplyArgs a, RingA
     w.sd = a.src + alpha;
     w.rd = r.dev + 2 * alpha + (DIR == kFwd ? 0 : 1);
     w.q = q;
-    w.in = DIR == kFwd ? (const V*)a.in + (a.in_mode == FM_DS_PER_PAIR ? (size_t)alpha * a.N * a.B : 0) + rhs0 : nullptr;
+    w.in = DIR == kFwd ? (const V*)a.in + (a.in_mode == FM_DS_PER_PAIR ? (size_t)alpha * a.N * a.B : 0) + rhs : nullptr;
     w.lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring_lds;
     w.stage_off = r.stage_off;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     if (wave < CW)
-        walk_narrow<DIR, V, RG, TB, D, QS, PS>(*w.rd, w, ring_lds, q, (int)threadIdx.x);
+        walk_narrow<DIR, V, TB, D, QS, PS>(*w.rd, w, ring_lds, q, (int)threadIdx.x);
     else if (wave < CW + OW)
-        walk_wide<DIR, V, RG, TB, DW, QS, PS>(*w.rd, w, ring_lds, q, (int)threadIdx.x - CW * 64);
+        walk_wide<DIR, V, TB, DW, QS, PS>(*w.rd, w, ring_lds, q, (int)threadIdx.x - CW * 64);
     else
-        walk_far<DIR, V, RG, TB, FW * 64, G, E, U, QS>(*w.rd, w, ring_lds, rv, a.B, r.F, (int)threadIdx.x - (CW + OW) * 64);
+        walk_far<DIR, V, TB, FW * 64, G, E, U, QS>(*w.rd, w, ring_lds, rv, a.B, r.F, (int)threadIdx.x - (CW + OW) * 64);
 }
 
 // ---------------------------------------------------------------------------
@@ -895,7 +821,7 @@ namespace {
 template <int DIR, typename V, int SH, bool QS, bool PS>
 const void* ring_fn() {
     constexpr Shape s = kShapes[SH];
-    return (const void*)k_ring<DIR, V, 1, s.cw, s.ow, s.fw, s.d, s.dw, s.g, s.e, s.u, QS, PS>;
+    return (const void*)k_ring<DIR, V, s.cw, s.ow, s.fw, s.d, s.dw, s.g, s.e, s.u, QS, PS>;
 }
 
 template <typename V, int SH>
@@ -1348,7 +1274,6 @@ hipError_t ring_walk(const fm_batch* b, bool fwd, const ApplyArgs& a0) {
     const RingPlan* r = b->ring;
     const bool fp64 = b->prec == FM_FP64;
     ApplyArgs a = a0;
-    a.ngroups = b->B;
     a.items = r->items;
     a.per_xcd = r->per_xcd;
     RingArgs ra{};
