@@ -70,10 +70,13 @@ constexpr int kChunk = 16;          // iterations between convergence checks
 constexpr int kTile = 64;           // words of 64 nodes listed by one wave
 constexpr int kThreads = 256;
 // Words (all sources) up to which an iteration is one launch, k_eik_word.  A
-// whole solve with it and with the lists: 2-D 77x40, 3 sources (192 words) 1.2
-// and 2.2 ms, 401x201, 1 and 4 sources (1280, 5120) 4.8 and 7.6, 7.1 and 9.3, 16
-// (20480) 13.9 and 10.4; 3-D 41x41x25, 1 source (704) 1.7 and 2.3, 8 (5632) 4.6
-// and 3.7, 101x101x51, 8 (65536) 53 and 19.
+// whole solve with it and with the lists: 2-D 401x201, 1, 4, 8 and 16 sources
+// (1280 words each) 4.3 and 7.4 ms, 7.1 and 9.7, 9.7 and 10.4, 14.4 and 11.5; 3-D
+// 41x41x25, 1, 2, 4 and 8 sources (704 words each) 1.9 and 2.7, 2.6 and 3.0, 3.4
+// and 3.5, 4.8 and 4.1; 60x60x35, 1 and 2 sources (1984 each) 3.3 and 3.8, 4.9 and
+// 4.6.  (One lane per node and a state byte, on the same sizes: 401x201, 1, 4 and
+// 16 sources 3.9, 8.6 and 23.9 ms; 41x41x25, 1, 4 and 16 2.1, 3.8 and 8.5; 77x40, 3
+// sources 1.24 against 1.07 with k_eik_word.)
 constexpr int64_t kSmall2 = 8192, kSmall3 = 2048;
 constexpr uint16_t kCopy = 1u << 15;   // list entry: the value is only copied
 
