@@ -895,9 +895,13 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     const int max_occ = shape == 0 ? 4 : shape == 1 ? 2 : 1;
     const int64_t pairs = (int64_t)S * B;
     const int occ = (int)std::min<int64_t>(std::max<int64_t>((pairs + cus - 1) / cus, 1), max_occ);
-    // At most two rounds of workgroups: 101x101x51 with 8 x 64 pairs, J 2.58 ms
-    // against the node split's 5.35, J^T 3.26 against 4.82; with 8 x 96 (three)
-    // 3.87 against 4.82 and 4.95 against 4.70.
+    // At most two rounds of workgroups.  J of the node split and of the walk,
+    // then J^T, FP64, for each of the three workgroups; two rounds: 101x101x51, 32
+    // sources x 16 right-hand sides, 3.23 and 2.62, 4.24 and 3.65 ms; 53x47x25,
+    // 32 x 32, 1.31 and 1.00, 1.57 and 1.33; 401x201, 64 x 32, 3.32 and 1.81, 3.68
+    // and 2.16.  Three rounds break even and take tables and inputs of their own:
+    // 48 x 16, 4.25 and 3.97, 5.61 and 5.52; 48 x 32, 1.37 and 1.41, 1.69 and 1.82;
+    // 96 x 32, 3.31 and 3.30, 3.90 and 3.77.
     if (pairs > (int64_t)cus * occ * 2) return FM_OK;
     const size_t budget = (size_t)160 * 1024 / occ - 512;
     const size_t stage = (size_t)stage_rows * sizeof(double);
@@ -1026,11 +1030,15 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     // Per direction the smallest side window that holds the entries of any two
     // consecutive chunks, taken where few enough neighbours are far: a far value
     // is a row of its own from the L2 or memory for every pair.  Far values per
-    // node against the time of the schedules below, 8 sources: beside the node
-    // split (16 right-hand sides) J 0.03: 0.98 ms for 1.87, 0.36: 5.1 for 3.9;
-    // J^T 0.10: 1.4 for 2.6, 0.20: 5.6 for 7.2, 0.38: 14.7 for 7.4.  Beside
-    // right-hand-side groups (one) J 0.36: 5.3 for 11.1, 0.69: 14.1 for 16.7;
-    // J^T 0.20: 6.2 for 12.9, 0.38: 15.5 for 13.4.
+    // node, the time of the schedule that runs otherwise and of the walk, FP64.
+    // Node split, J: 0.03 (101x101x51, 16 sources x 16 right-hand sides) 2.95 and
+    // 1.38 ms, 0.13 (121x121x61, 8 x 8) 3.49 and 2.33, 0.36 (141x141x71, 8 x 16)
+    // 5.55 and 5.31, 0.35 (201x201x51, 8 x 16) 6.65 and 7.79, 0.54 (161x161x81, 8 x
+    // 16) 7.37 and 8.92; J^T: 0.10 3.69 and 1.85, 0.11 4.13 and 3.35, 0.13 and 0.23
+    // (141x141x71, two placements of the sources) 4.9 and 3.7, 6.8 and 4.2, so that
+    // the line is on the safe side there.  Right-hand-side groups, 8 x 1, J: 0.35
+    // 17.1 and 8.5, 0.36 12.0 and 5.4, 0.54 17.5 and 9.5, 0.69 16.7 and 14.1; J^T: 0.13
+    // 10.3 and 4.6, 0.20 14.5 and 6.7, 0.38 13.4 and 15.5.
     const double far_max[2] = {b->tun.split > 1 ? 0.2 : 0.5, b->tun.split > 1 ? 0.2 : 0.3};
     int pick[2] = {-1, -1};
     for (int dir = 0; dir < 2; dir++) {
