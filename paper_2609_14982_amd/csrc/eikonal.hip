@@ -32,10 +32,10 @@
 
 #include <algorithm>
 #include <cmath>
-#include <utility>
 #include <vector>
 
 #include "fmbtf.h"
+#include "devmem.h"
 #include "internal.h"
 #include "batch.h"
 
@@ -46,7 +46,7 @@ struct fm_eikonal {
     int32_t S = 0;                  // capacity in sources
     double* X = nullptr;            // device [N][dim]
     double* Tb = nullptr;           // device [S][N] second buffer
-    void* block = nullptr;          // holds the device arrays below
+    fm::DevBlocks block;            // holds the device arrays below
     int64_t W = 0;                  // words of 64 nodes per source (a multiple of kTile)
     uint16_t* list = nullptr;       // device [S][W / 64][4096] nodes of a tile to recompute
     int32_t* count = nullptr;       // device [S][W / 64] their number
@@ -158,11 +158,14 @@ __device__ __forceinline__ double tri_inner(const double* xi, double si, const d
 
 // Seeds and +inf in both buffers (an iteration leaves a node's value in the
 // buffer it writes untouched when that buffer already holds it), and the seeds
-// as the nodes changed last: one wave per word, one lane per node.
+// as the nodes changed last: one wave per word, one lane per node.  The first
+// source's waves also write the nodes with a lower and an upper neighbour on
+// axes 0 and 1 (the last axis needs none: its shifts leave the grid).
 __global__ __launch_bounds__(kThreads) void k_eik_init(EikDims d, int32_t S, const double* __restrict__ X,
                                                        const double* __restrict__ s, const double* __restrict__ xi,
                                                        double rho, double* __restrict__ T, double* __restrict__ T2,
-                                                       uint64_t* __restrict__ chg, uint64_t* __restrict__ seeds) {
+                                                       uint64_t* __restrict__ chg, uint64_t* __restrict__ seeds,
+                                                       uint64_t* __restrict__ edge) {
     const int64_t total = (int64_t)S * d.W;
     for (int64_t i = (blockIdx.x * (int64_t)kThreads + threadIdx.x) / 64; i < total; i += (int64_t)gridDim.x * (kThreads / 64)) {
         const int64_t alpha = i / d.W, p = (i - alpha * d.W) * 64 + (threadIdx.x & 63);
@@ -176,6 +179,13 @@ __global__ __launch_bounds__(kThreads) void k_eik_init(EikDims d, int32_t S, con
         if ((threadIdx.x & 63) == 0) {
             chg[i] = word;
             seeds[i] = word;
+        }
+        if (alpha == 0) {
+            const bool in = p < d.N;
+            const uint64_t w[4] = {__ballot(in && c[0] > 0), __ballot(in && c[0] < d.n0 - 1), __ballot(in && c[1] > 0),
+                                   __ballot(in && c[1] < d.n1 - 1)};
+            if ((threadIdx.x & 63) == 0)
+                for (int k = 0; k < 4; ++k) edge[k * d.W + i] = w[k];
         }
         if (p >= d.N) continue;
         if (!seed) {
@@ -210,21 +220,6 @@ __global__ __launch_bounds__(kThreads) void k_eik_init(EikDims d, int32_t S, con
         const double v = 0.5 * (s_src + s[p]) * dist(X + p * d.dim, x_src, d.dim);
         T[t] = v;
         T2[t] = v;
-    }
-}
-
-// Nodes with a lower and an upper neighbour on axes 0 and 1 (the last axis
-// needs none: its shifts leave the grid).
-__global__ __launch_bounds__(kThreads) void k_eik_edges(EikDims d, uint64_t* __restrict__ edge) {
-    for (int64_t i = (blockIdx.x * (int64_t)kThreads + threadIdx.x) / 64; i < d.W; i += (int64_t)gridDim.x * (kThreads / 64)) {
-        const int64_t p = i * 64 + (threadIdx.x & 63);
-        int64_t c[3];
-        logical(d, p, c);
-        const bool in = p < d.N;
-        const uint64_t w[4] = {__ballot(in && c[0] > 0), __ballot(in && c[0] < d.n0 - 1), __ballot(in && c[1] > 0),
-                               __ballot(in && c[1] < d.n1 - 1)};
-        if ((threadIdx.x & 63) == 0)
-            for (int k = 0; k < 4; ++k) edge[k * d.W + i] = w[k];
     }
 }
 
@@ -475,38 +470,22 @@ int fm_eikonal_create(int32_t dim, int64_t n1, int64_t n2, int64_t n3, const dou
     if (h == hipSuccess) h = hipMalloc(&e->X, sizeof(double) * (size_t)N * dim);
     if (h == hipSuccess) h = hipMalloc(&e->Tb, sizeof(double) * nsn);
     e->W = (N + 64 * kTile - 1) / (64 * kTile) * kTile;
-    // one allocation for the small arrays (0.2 ms each otherwise), 256-byte parts
     const size_t src = (size_t)max_sources, W = (size_t)e->W;
-    const std::pair<void**, size_t> parts[] = {{(void**)&e->chg[0], sizeof(uint64_t) * src * W},
-                                               {(void**)&e->chg[1], sizeof(uint64_t) * src * W},
-                                               {(void**)&e->seed, sizeof(uint64_t) * src * W},
-                                               {(void**)&e->edge, sizeof(uint64_t) * 4 * W},
-                                               {(void**)&e->list, sizeof(uint16_t) * 64 * src * W},
-                                               {(void**)&e->count, sizeof(int32_t) * src * (W / kTile)},
-                                               {(void**)&e->batch, sizeof(uint32_t) * src * W},
-                                               {(void**)&e->xi, sizeof(double) * 3 * src},
-                                               {(void**)&e->n_batch, sizeof(unsigned) * (kChunk + 1)}};
-    size_t all = 0;
-    for (const auto& x : parts) all += (x.second + 255) & ~size_t(255);
-    if (h == hipSuccess) h = hipMalloc(&e->block, all);
-    if (h == hipSuccess) {
-        char* at = (char*)e->block;
-        for (const auto& x : parts) {
-            *x.first = at;
-            at += (x.second + 255) & ~size_t(255);
-        }
-    }
+    if (h == hipSuccess)
+        h = e->block.take({{(void**)&e->chg[0], sizeof(uint64_t) * src * W},
+                           {(void**)&e->chg[1], sizeof(uint64_t) * src * W},
+                           {(void**)&e->seed, sizeof(uint64_t) * src * W},
+                           {(void**)&e->edge, sizeof(uint64_t) * 4 * W},
+                           {(void**)&e->list, sizeof(uint16_t) * 64 * src * W},
+                           {(void**)&e->count, sizeof(int32_t) * src * (W / kTile)},
+                           {(void**)&e->batch, sizeof(uint32_t) * src * W},
+                           {(void**)&e->xi, sizeof(double) * 3 * src},
+                           {(void**)&e->n_batch, sizeof(unsigned) * (kChunk + 1)}});
     int cus = 0;
     if (h == hipSuccess) h = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, e->device);
     e->waves = cus * 24;    // 12 a CU are resident; more for the batches' different lengths
     if (h == hipSuccess) h = hipHostMalloc((void**)&e->n_batch_h, sizeof(unsigned) * (kChunk + 1), hipHostMallocDefault);
     if (h == hipSuccess) h = hipMemcpy(e->X, X, sizeof(double) * (size_t)N * dim, hipMemcpyHostToDevice);
-    if (h == hipSuccess) {
-        hipLaunchKernelGGL(k_eik_edges, dim3((unsigned)std::min<int64_t>((e->W + 3) / 4, 4096)), dim3(kThreads), 0, nullptr,
-                           EikDims{e->dim, e->n[0], e->n[1], e->n[2], e->N, e->W}, e->edge);
-        h = hipGetLastError();
-        if (h == hipSuccess) h = hipStreamSynchronize(nullptr);
-    }
     if (h != hipSuccess) {
         set_error("first-arrival solver allocation failed: %s", hipGetErrorString(h));
         fm_eikonal_free(e);
@@ -562,7 +541,7 @@ int fm_eikonal_solve(fm_eikonal* e, const double* s, int32_t S, const double* xi
     const int tiles = (int)std::min<int64_t>(((int64_t)S * (e->W / kTile) + 3) / 4, 16384);
     double* buf[2] = {T, e->Tb};
     hipLaunchKernelGGL(k_eik_init, dim3(grid), dim3(256), 0, st, d, S, e->X, s, e->xi, seed_radius, buf[0], buf[1],
-                       e->chg[0], e->seed);
+                       e->chg[0], e->seed, e->edge);
     HIP_TRY(hipGetLastError());
     const auto list_fn = e->dim == 3 ? k_eik_list<3> : k_eik_list<2>;
     const auto step_fn = e->dim == 3 ? k_eik_step<3> : k_eik_step<2>;
@@ -615,7 +594,7 @@ void fm_eikonal_free(fm_eikonal* e) {
     if (!e) return;
     if (e->X) (void)hipFree(e->X);
     if (e->Tb) (void)hipFree(e->Tb);
-    if (e->block) (void)hipFree(e->block);
+    e->block.release();
     if (e->n_batch_h) (void)hipHostFree(e->n_batch_h);
     delete e;
 }
