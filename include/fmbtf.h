@@ -315,9 +315,15 @@ void fm_state_free(fm_state* st);
 /*
  * Create a batch over S states for B right-hand sides in FM_FP64 or FM_FP32
  * on the current HIP device.  Uploads the states that are not yet on the
- * device and allocates all scratch ([S][N][B] of the batch precision, twice
- * and 36 to 44 bytes per node and source where the LDS window walk is taken,
- * fm_tuning) so that the apply calls allocate nothing.  tuning may be NULL.  hip_stream is a
+ * device and allocates all scratch ([S][N][B] of the batch precision) so that
+ * the apply calls allocate nothing.  Where the LDS window walk is taken
+ * (fm_tuning) it allocates the same again for the inputs in level order, and
+ * tables: per node and source 36 bytes for J and 44 for J^T in FP64, 28 each in
+ * FP32; per node of more than three neighbours or in an SCC block 80 (FP64) or
+ * 48 more for each direction; 4 per value outside the window; and until the
+ * call returns 10 per node and source.  Which kernel runs depends on the free
+ * memory at this call, and the last bits of block members on the kernel: their
+ * sums are grouped by its workgroups.  tuning may be NULL.  hip_stream is a
  * hipStream_t (NULL: the null stream).  All states must share one grid shape.
  * Errors: FM_EINVAL, FM_ENOMEM, FM_EHIP.
  */
@@ -546,7 +552,7 @@ void fm_cgls_free(fm_cgls* C);
  *
  * fm_eikonal_create: X host [N][dim] physical node coordinates (copied);
  *   room for up to max_sources sources per solve (device scratch of
- *   max_sources x N x 10 bytes); work is enqueued on hip_stream (NULL: the
+ *   max_sources x N x 10.5 bytes, N rounded up to 4096 for 2.5 of them); work is enqueued on hip_stream (NULL: the
  *   null stream).
  * fm_eikonal_solve: s device [N] slowness (finite, > 0), xi_src host [S][dim]
  *   logical source coordinates in [0, n_d - 1], seed_radius >= 0 logical

@@ -7,9 +7,10 @@
 // a 101x101x51 grid), the rhs-group kernel store, barrier and load in its own
 // CU plus the scattered accesses of one CU (4.4 us).  A workgroup that owns a
 // level alone can keep the values of the last C positions of its walk in LDS
-// (160 KB hold 16,500 FP64 values, five to ten levels of that grid), so that a
-// level's chain is three LDS reads, three FMAs, one LDS write and a workgroup
-// barrier, and everything it streams is known ahead of time:
+// (160 KB hold 15,300 to 19,100 FP64 values beside the far ones, five to ten
+// levels of that grid), so that a level's chain is three LDS reads, three FMAs,
+// one LDS write and a workgroup barrier, and everything it streams is known
+// ahead of time:
 //   - per node, in level order: the LDS slots of its neighbours, its node id,
 //     its weights and its right-hand side q, permuted to level order by a pass
 //     before the walk; all are loaded D batches ahead;
@@ -32,14 +33,15 @@
 // A node's sum is taken in the order of the other kernels (q, then its
 // neighbours by ascending slot; unused slots add 0 * 0).
 //
-// Measured against the schedule it replaces (input pass and walk together):
-// 101x101x51, 8 sources x 16 right-hand sides, FP64: J 2.52 -> 1.14 ms, J^T
-// summed 3.31 -> 1.56 ms; 8 sources x 1: J 3.50 -> 0.80 ms, J^T 2.89 -> 1.03 ms;
-// 121x97x57, 6 x 16, FP32: J to every node 4.79 -> 1.78 ms; 67x53x31, 5 x 5, FP64:
-// J^T per source 1.22 -> 0.49 ms; 81x41, one pair: J 122 -> 34 us, J^T 167 -> 37 us.  What bounds it now is the
-// bytes one CU keeps in flight: 44 a node (36 with receiver input) arrive at
-// some 32 GB/s however many batches are loaded ahead (3 to 8: the same time),
-// and without the weights' load the walk takes half as long.
+// Measured against the schedule it replaces, whole applies whose inputs change
+// from pass to pass: 101x101x51, 8 sources x 16 right-hand sides, FP64: J 2.80 ->
+// 1.12 ms, J^T summed 3.64 -> 1.62 ms; 121x97x57, 6 x 16, FP32: J to every node
+// 5.52 -> 1.76 ms; 67x53x31, 5 x 5, FP64: J^T per source 1.28 -> 0.54 ms; 81x41, one
+// pair: J 149 -> 40 us, J^T 199 -> 43 us; the same inputs again, 101x101x51, 8 x 1: J
+// 3.50 -> 0.79 ms, J^T 2.89 -> 1.23 ms.  What bounds it now is the bytes one CU
+// keeps in flight: 44 a node (36 with receiver input) arrive at some 32 GB/s
+// however many batches are loaded ahead (3 to 8: the same time), and without the
+// weights' load the walk takes half as long.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
