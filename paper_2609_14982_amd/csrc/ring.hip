@@ -859,6 +859,107 @@ struct Bytes {
     }
 };
 
+// The levels of one direction of one source in chunks of at most `most`
+// singletons, the level's blocks with its last chunk: each is a step of the walk
+// of its own, so that a wide level needs no more of the window than its own
+// values and one chunk.
+struct Chunks {
+    std::vector<int32_t> pos, n, lev;   // first position of each and the end, singletons, level
+    Chunks(const std::vector<int32_t>& ptr, const std::vector<int32_t>& nsc, int32_t most) {
+        for (int32_t l = 0; l + 1 < (int32_t)ptr.size(); l++)
+            for (int32_t o = 0; o == 0 || o < nsc[l]; o += most) {
+                pos.push_back(ptr[l] + o);
+                n.push_back(std::min(most, nsc[l] - o));
+                lev.push_back(l);
+            }
+        pos.push_back(ptr.back());
+    }
+    int32_t size() const { return (int32_t)n.size(); }
+    // any k consecutive chunks span at most c positions
+    bool fit(int32_t k, int32_t c) const {
+        const int32_t L = size();
+        for (int32_t l = 0; l < L; l++)
+            if (pos[std::min(l + k, L)] - pos[l] > c) return false;
+        return true;
+    }
+};
+
+// The walk's lists of one direction of one source.
+struct Lists {
+    std::vector<uint2> nd;
+    std::vector<uint4> wd, fd;
+    std::vector<int4> lv;      // (BuildDev::lv)
+    std::vector<int32_t> bw;   // first wide record of each block's members
+    int64_t n_far = 0, n_wide = 0;
+};
+
+constexpr int kPad = 16;       // half the empty batches past the end (the walk loads up to 3 D or 1 + G + 2 E ahead)
+
+// cnt [chunks][kCand + 2] as counted, c the window taken.
+Lists walk_lists(const Packed& pk, bool fwd, const Chunks& ch, const int32_t* cnt, int c, int32_t C, int32_t F,
+                 const Shape& sh) {
+    Lists t;
+    const int NL = sh.cw * 64, OL = sh.ow * 64;
+    const std::vector<int32_t>& bptr = fwd ? pk.fblk_ptr : pk.rblk_ptr;
+    const std::vector<int32_t>& bid = fwd ? pk.fblk_id : pk.rblk_id;
+    const std::vector<int32_t>& bpos = fwd ? pk.blk_fpos : pk.blk_rpos;
+    const int32_t L = ch.size();
+    t.fd.assign(sh.e, uint4{0u, 0u, 0u, 0u});
+    // rows are drained every K chunks, as rarely as the window allows
+    int32_t K = 16;
+    while (K > 1 && !ch.fit(K + sh.g + 1, C)) --K;
+    int32_t skip = 0;
+    bool dirty = false;
+    t.bw.assign(std::max<size_t>(pk.blk_k.size(), 1), 0);
+    for (int32_t l = 0; l < L; l++, cnt += kCand + 2) {
+        const int32_t p0 = ch.pos[l], p1 = ch.pos[l + 1], ns = ch.n[l];
+        const int32_t few = cnt[kCand + 1], nw = ns - few, nf = cnt[c] + cnt[kCand];
+        const bool blk = p1 - p0 > ns;       // members follow the singletons
+        const uint32_t fl = (blk ? kBlk : 0u) | (l % K == K - 1 ? kDrain : 0u);
+        t.lv.push_back(int4{(int)t.n_wide, (int)t.n_far, (int)(t.n_far % F), few});
+        t.fd.push_back(uint4{(uint32_t)t.n_far, (uint32_t)nf, kLast | fl, (uint32_t)(t.n_far % F)});
+        for (int32_t o = 0; o == 0 || o < few; o += NL) {
+            const int32_t n = std::min(few - o, NL);
+            t.nd.push_back(uint2{(uint32_t)(p0 + o),
+                                 (uint32_t)n | (o + NL >= few ? kLast | fl : 0u) | (uint32_t)((p0 + o) % C) << 16});
+        }
+        // (a level where these waves have nothing to do is passed over: no
+        // node, no block, and no store of theirs since the last drain)
+        const int32_t q0 = p0 + few;
+        dirty = dirty || nw > 0;
+        if (nw == 0 && l + 1 < L && !(fl & kBlk) && !((fl & kDrain) && dirty)) {
+            ++skip;
+        } else {
+            for (int32_t o = 0; o == 0 || o < nw; o += OL) {
+                const int32_t n = std::min(nw - o, OL);
+                t.wd.push_back(uint4{(uint32_t)(q0 + o),
+                                     (uint32_t)n | (o + OL >= nw ? kLast | fl : 0u) | (uint32_t)((q0 + o) % C) << 16,
+                                     (uint32_t)(t.n_wide + o), (uint32_t)skip});
+                skip = 0;
+            }
+            if (fl & kDrain) dirty = false;
+        }
+        if (blk)
+            for (int32_t b = bptr[ch.lev[l]]; b < bptr[ch.lev[l] + 1]; b++)
+                t.bw[bid[b]] = (int32_t)(t.n_wide + nw + bpos[bid[b]] - (p0 + ns));
+        // the rest of the round after a level with blocks is empty
+        if (fl & kBlk) {
+            while (t.nd.size() % sh.d) t.nd.push_back(uint2{0u, 0u});
+            while (t.wd.size() % sh.dw) t.wd.push_back(uint4{0u, 0u, 0u, 0u});
+            while (t.fd.size() % sh.e) t.fd.push_back(uint4{0u, 0u, 0u, 0u});
+        }
+        t.n_far += nf;
+        t.n_wide += p1 - p0 - few;
+    }
+    t.lv.push_back(int4{(int)t.n_wide, (int)t.n_far, 0, 0});
+    while (t.fd.size() % sh.e) t.fd.push_back(uint4{0u, 0u, 0u, 0u});
+    // batches past the end load the first position again
+    t.nd.insert(t.nd.end(), 2 * kPad, uint2{0u, 0u});
+    t.wd.insert(t.wd.end(), 2 * kPad, uint4{0u, 0u, 0u, 0u});
+    t.fd.insert(t.fd.end(), 2 * kPad, uint4{0u, 0u, 0u, 0u});
+    return t;
+}
+
 }  // namespace
 
 static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPlan** out) {
@@ -920,41 +1021,22 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     // source: temporary buffers of the passes below
     Bytes tb;
     std::vector<BuildDev> bd(nd);
-    // levels in chunks of at most `chunk` singletons, the level's blocks with its
-    // last chunk: each is a step of the walk of its own, so that a wide level
-    // needs no more of the window than its own values and one chunk
-    const int32_t chunk = 2 * sh.cw * 64;
-    std::vector<std::vector<int32_t>> cp(nd), cn(nd), cl(nd);   // positions, singletons, level
+    std::vector<Chunks> ch;
     int32_t max_c = 0;
     for (int i = 0; i < nd; i++) {
         const Packed& pk = b->states[i / 2]->pk;
-        const std::vector<int32_t>& lp = i % 2 == 0 ? pk.flvl_ptr : pk.rlvl_ptr;
-        const std::vector<int32_t>& ls = i % 2 == 0 ? pk.flvl_nsc : pk.rlvl_nsc;
-        for (int32_t l = 0; l + 1 < (int32_t)lp.size(); l++)
-            for (int32_t o = 0; o == 0 || o < ls[l]; o += chunk) {
-                cp[i].push_back(lp[l] + o);
-                cn[i].push_back(std::min(chunk, ls[l] - o));
-                cl[i].push_back(l);
-            }
-        cp[i].push_back(lp.back());
-        max_c = std::max(max_c, (int32_t)cn[i].size());
+        if (i % 2 == 0) ch.emplace_back(pk.flvl_ptr, pk.flvl_nsc, 2 * sh.cw * 64);
+        else ch.emplace_back(pk.rlvl_ptr, pk.rlvl_nsc, 2 * sh.cw * 64);
+        // a far value is drained and loaded between its chunk and its reader's:
+        // K + G + 1 chunks have to fit (K = 1 drains every chunk)
+        if (!ch[i].fit(sh.g + 2, C[0])) return FM_OK;
+        max_c = std::max(max_c, ch[i].size());
     }
-    // a far value is drained and loaded between its chunk and its reader's:
-    // K + G + 1 chunks have to fit (K = 1 drains every chunk)
-    auto fits = [&](int i, int32_t n, int32_t c) {
-        const std::vector<int32_t>& lp = cp[i];
-        const int32_t L = (int32_t)lp.size() - 1;
-        for (int32_t l = 0; l < L; l++)
-            if (lp[std::min(l + n, L)] - lp[l] > c) return false;
-        return true;
-    };
-    for (int i = 0; i < nd; i++)
-        if (!fits(i, sh.g + 2, C[0])) return FM_OK;
     std::vector<size_t> o_cp(nd), o_cn(nd), o_cl(nd);
     for (int i = 0; i < nd; i++) {
-        o_cp[i] = tb.add(sizeof(int32_t) * cp[i].size());
-        o_cn[i] = tb.add(sizeof(int32_t) * cn[i].size());
-        o_cl[i] = tb.add(sizeof(int32_t) * cl[i].size());
+        o_cp[i] = tb.add(sizeof(int32_t) * ch[i].pos.size());
+        o_cn[i] = tb.add(sizeof(int32_t) * ch[i].n.size());
+        o_cl[i] = tb.add(sizeof(int32_t) * ch[i].lev.size());
     }
     const size_t o_bd = tb.add(sizeof(BuildDev) * nd);
     const size_t head_end = tb.off;
@@ -962,7 +1044,7 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     size_t n_cnt = 0;
     for (int i = 0; i < nd; i++) {
         o_cnt[i] = n_cnt;
-        n_cnt += (kCand + 2) * cn[i].size();
+        n_cnt += (kCand + 2) * ch[i].n.size();
     }
     struct Temp {
         DevBlocks mem;
@@ -996,7 +1078,7 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         x.rcv_pos = fwd || d.n_ent == 0 ? nullptr : d.rcv_pos;
         x.rcv_node = d.rcv_node;
         x.n_rcv_node = fwd ? d.n_ent : 0;
-        x.L = (int32_t)cn[i].size();
+        x.L = ch[i].size();
         x.pos = temp.pos + (size_t)i * N;
         x.need = temp.need + (size_t)i * N;
         x.cnt = temp.cnt + o_cnt[i];
@@ -1010,9 +1092,9 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     {
         std::vector<char> head(head_end);
         for (int i = 0; i < nd; i++) {
-            memcpy(head.data() + o_cp[i], cp[i].data(), sizeof(int32_t) * cp[i].size());
-            memcpy(head.data() + o_cn[i], cn[i].data(), sizeof(int32_t) * cn[i].size());
-            memcpy(head.data() + o_cl[i], cl[i].data(), sizeof(int32_t) * cl[i].size());
+            memcpy(head.data() + o_cp[i], ch[i].pos.data(), sizeof(int32_t) * ch[i].pos.size());
+            memcpy(head.data() + o_cn[i], ch[i].n.data(), sizeof(int32_t) * ch[i].n.size());
+            memcpy(head.data() + o_cl[i], ch[i].lev.data(), sizeof(int32_t) * ch[i].lev.size());
         }
         memcpy(head.data() + o_bd, bd.data(), sizeof(BuildDev) * nd);
         e = hipMemcpy(tmp, head.data(), head_end, hipMemcpyHostToDevice);
@@ -1055,7 +1137,7 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
                     far += count(i, l, c);
                     ok = two <= F[c];
                 }
-                ok = ok && fits(i, sh.g + 2, C[c]);
+                ok = ok && ch[i].fit(sh.g + 2, C[c]);
             }
             if (ok && (double)far <= far_max[dir] * (double)S * (double)N) pick[dir] = c;
         }
@@ -1076,89 +1158,22 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     const size_t win = (((size_t)(std::max(r->C[0] + r->F[0], r->C[1] + r->F[1]) + 1) * vb) + 15) & ~size_t(15);
     r->stage_off = (int32_t)win;
     r->lds = win + stage;
-    // host tables: batches, far ranges, level offsets
-    const int NL = sh.cw * 64, OL = sh.ow * 64;
-    constexpr int kPad = 16;     // half the empty batches past the end (the walk loads up to 3 D or 1 + G + 2 E ahead)
-    std::vector<std::vector<uint2>> ndl(nd);
-    std::vector<std::vector<uint4>> wdl(nd), fdl(nd);
-    std::vector<std::vector<int4>> lv(nd);
-    std::vector<std::vector<int32_t>> bw(nd);
-    std::vector<int64_t> n_far(nd, 0), n_wide(nd, 0);
-    for (int i = 0; i < nd; i++) {
-        if (!bd[i].C) continue;
-        const Packed& pk = b->states[i / 2]->pk;
-        const std::vector<int32_t>&lp = cp[i], &ns = cn[i];
-        const std::vector<int32_t>& bptr = i % 2 == 0 ? pk.fblk_ptr : pk.rblk_ptr;
-        const std::vector<int32_t>& bid = i % 2 == 0 ? pk.fblk_id : pk.rblk_id;
-        const std::vector<int32_t>& bpos = i % 2 == 0 ? pk.blk_fpos : pk.blk_rpos;
-        const int32_t L = bd[i].L;
-        fdl[i].assign(sh.e, uint4{0u, 0u, 0u, 0u});
-        // rows are drained every K chunks, as rarely as the window allows
-        int32_t K = 16;
-        while (K > 1 && !fits(i, K + sh.g + 1, bd[i].C)) --K;
-        int32_t skip = 0;
-        bool dirty = false;
-        bw[i].assign(std::max<size_t>(pk.blk_k.size(), 1), 0);
-        for (int32_t l = 0; l < L; l++) {
-            const int32_t p0 = lp[l], few = count(i, l, kCand + 1), nw = ns[l] - few;
-            const int32_t lev = cl[i][l];
-            const bool blk = lp[l + 1] - lp[l] > ns[l];   // members follow the singletons
-            const uint32_t fl = (blk ? kBlk : 0u) | (l % K == K - 1 ? kDrain : 0u);
-            const int32_t nf = count(i, l, pick[i % 2]) + count(i, l, kCand);
-            lv[i].push_back(int4{(int)n_wide[i], (int)n_far[i], (int)(n_far[i] % bd[i].F), few});
-            fdl[i].push_back(uint4{(uint32_t)n_far[i], (uint32_t)nf, kLast | fl, (uint32_t)(n_far[i] % bd[i].F)});
-            for (int32_t o = 0; o == 0 || o < few; o += NL) {
-                const int32_t c = std::min(few - o, NL);
-                ndl[i].push_back(uint2{(uint32_t)(p0 + o), (uint32_t)c | (o + NL >= few ? kLast | fl : 0u) |
-                                                               (uint32_t)((p0 + o) % bd[i].C) << 16});
-            }
-            // (a level where these waves have nothing to do is passed over: no
-            // node, no block, and no store of theirs since the last drain)
-            const int32_t q0 = p0 + few;
-            dirty = dirty || nw > 0;
-            if (nw == 0 && l + 1 < L && !(fl & kBlk) && !((fl & kDrain) && dirty)) {
-                ++skip;
-            } else {
-                for (int32_t o = 0; o == 0 || o < nw; o += OL) {
-                    const int32_t c = std::min(nw - o, OL);
-                    wdl[i].push_back(uint4{(uint32_t)(q0 + o), (uint32_t)c | (o + OL >= nw ? kLast | fl : 0u) |
-                                                                   (uint32_t)((q0 + o) % bd[i].C) << 16,
-                                           (uint32_t)(n_wide[i] + o), (uint32_t)skip});
-                    skip = 0;
-                }
-                if (fl & kDrain) dirty = false;
-            }
-            for (int32_t t = bptr[lev]; blk && t < bptr[lev + 1]; t++)
-                bw[i][bid[t]] = (int32_t)(n_wide[i] + nw + bpos[bid[t]] - (p0 + ns[l]));
-            // the rest of the round after a level with blocks is empty
-            if (fl & kBlk) {
-                while (ndl[i].size() % sh.d) ndl[i].push_back(uint2{0u, 0u});
-                while (wdl[i].size() % sh.dw) wdl[i].push_back(uint4{0u, 0u, 0u, 0u});
-                while (fdl[i].size() % sh.e) fdl[i].push_back(uint4{0u, 0u, 0u, 0u});
-            }
-            n_far[i] += nf;
-            n_wide[i] += lp[l + 1] - p0 - few;
-        }
-        lv[i].push_back(int4{(int)n_wide[i], (int)n_far[i], 0, 0});
-        while (fdl[i].size() % sh.e) fdl[i].push_back(uint4{0u, 0u, 0u, 0u});
-        // batches past the end load the first position again
-        for (int t = 0; t < 2 * kPad; t++) {
-            ndl[i].push_back(uint2{0u, 0u});
-            wdl[i].push_back(uint4{0u, 0u, 0u, 0u});
-            fdl[i].push_back(uint4{0u, 0u, 0u, 0u});
-        }
-    }
+    std::vector<Lists> li(nd);
+    for (int i = 0; i < nd; i++)
+        if (bd[i].C)
+            li[i] = walk_lists(b->states[i / 2]->pk, i % 2 == 0, ch[i], cnt.data() + o_cnt[i], pick[i % 2], bd[i].C,
+                               bd[i].F, sh);
     Bytes pb;
     const size_t o_dev = pb.add(sizeof(RingDev) * nd), o_build = pb.add(sizeof(BuildDev) * nd);
     std::vector<size_t> o_nd(nd), o_wd(nd), o_fd(nd), o_lv(nd), o_bw(nd), o_lev(nd);
     for (int i = 0; i < nd; i++) {
         if (!bd[i].C) continue;
-        o_nd[i] = pb.add(sizeof(uint2) * ndl[i].size());
-        o_wd[i] = pb.add(sizeof(uint4) * wdl[i].size());
-        o_fd[i] = pb.add(sizeof(uint4) * fdl[i].size());
-        o_lv[i] = pb.add(sizeof(int4) * lv[i].size());
-        o_bw[i] = pb.add(sizeof(int32_t) * bw[i].size());
-        o_lev[i] = pb.add(sizeof(int32_t) * cl[i].size());
+        o_nd[i] = pb.add(sizeof(uint2) * li[i].nd.size());
+        o_wd[i] = pb.add(sizeof(uint4) * li[i].wd.size());
+        o_fd[i] = pb.add(sizeof(uint4) * li[i].fd.size());
+        o_lv[i] = pb.add(sizeof(int4) * li[i].lv.size());
+        o_bw[i] = pb.add(sizeof(int32_t) * li[i].bw.size());
+        o_lev[i] = pb.add(sizeof(int32_t) * ch[i].lev.size());
     }
     const size_t host_end = pb.add(0);
     // one array per stream over all sources (every source on a 256-byte boundary)
@@ -1171,9 +1186,9 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         o_wa[i] = st_wa.add((size_t)N * 16);
         o_wb[i] = st_wb.add(fp64 ? (size_t)N * 8 : 0);
         o_wc[i] = st_wc.add(fp64 && i % 2 ? (size_t)N * 8 : 0);
-        o_wref[i] = st_wref.add((size_t)(n_wide[i] + 1) * 16);
-        o_wwt[i] = st_wwt.add((size_t)(n_wide[i] + 1) * 8 * vb);
-        o_far[i] = st_far.add((size_t)(n_far[i] + 1) * 4);
+        o_wref[i] = st_wref.add((size_t)(li[i].n_wide + 1) * 16);
+        o_wwt[i] = st_wwt.add((size_t)(li[i].n_wide + 1) * 8 * vb);
+        o_far[i] = st_far.add((size_t)(li[i].n_far + 1) * 4);
     }
     // at most a quarter of the free memory: a program that sized its own arrays
     // by a batch's scratch rows keeps its room
@@ -1196,12 +1211,12 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
     std::vector<RingDev> rd(nd);
     for (int i = 0; i < nd; i++) {
         if (!bd[i].C) continue;
-        memcpy(hb.data() + o_nd[i], ndl[i].data(), sizeof(uint2) * ndl[i].size());
-        memcpy(hb.data() + o_wd[i], wdl[i].data(), sizeof(uint4) * wdl[i].size());
-        memcpy(hb.data() + o_fd[i], fdl[i].data(), sizeof(uint4) * fdl[i].size());
-        memcpy(hb.data() + o_lv[i], lv[i].data(), sizeof(int4) * lv[i].size());
-        memcpy(hb.data() + o_bw[i], bw[i].data(), sizeof(int32_t) * bw[i].size());
-        memcpy(hb.data() + o_lev[i], cl[i].data(), sizeof(int32_t) * cl[i].size());
+        memcpy(hb.data() + o_nd[i], li[i].nd.data(), sizeof(uint2) * li[i].nd.size());
+        memcpy(hb.data() + o_wd[i], li[i].wd.data(), sizeof(uint4) * li[i].wd.size());
+        memcpy(hb.data() + o_fd[i], li[i].fd.data(), sizeof(uint4) * li[i].fd.size());
+        memcpy(hb.data() + o_lv[i], li[i].lv.data(), sizeof(int4) * li[i].lv.size());
+        memcpy(hb.data() + o_bw[i], li[i].bw.data(), sizeof(int32_t) * li[i].bw.size());
+        memcpy(hb.data() + o_lev[i], ch[i].lev.data(), sizeof(int32_t) * ch[i].lev.size());
         rd[i].ref = (const uint2*)(ref + o_ref[i]);
         rd[i].node = (const uint32_t*)(node + o_node[i]);
         rd[i].wa = wa + o_wa[i];
@@ -1214,9 +1229,9 @@ static int ring_build(const fm_batch* b, const std::vector<SrcDev>& src, RingPla
         rd[i].fd = (const uint4*)(tab + o_fd[i]);
         rd[i].far = (const uint32_t*)(far + o_far[i]);
         rd[i].blk_w = (const int32_t*)(tab + o_bw[i]);
-        rd[i].n_nd = (int32_t)ndl[i].size() - 2 * kPad;
-        rd[i].n_wd = (int32_t)wdl[i].size() - 2 * kPad;
-        rd[i].n_fd = (int32_t)fdl[i].size() - 2 * kPad - sh.e;
+        rd[i].n_nd = (int32_t)li[i].nd.size() - 2 * kPad;
+        rd[i].n_wd = (int32_t)li[i].wd.size() - 2 * kPad;
+        rd[i].n_fd = (int32_t)li[i].fd.size() - 2 * kPad - sh.e;
         rd[i].lev = (const int32_t*)(tab + o_lev[i]);
         bd[i].ref = (uint2*)(ref + o_ref[i]);
         bd[i].node = (uint32_t*)(node + o_node[i]);
