@@ -44,10 +44,11 @@ struct fm_eikonal {
     int64_t n[3] = {1, 1, 1};
     int64_t N = 0;
     int32_t S = 0;                  // capacity in sources
+    fm::DevBlocks block;            // holds the device arrays below
     double* X = nullptr;            // device [N][dim]
     double* Tb = nullptr;           // device [S][N] second buffer
-    fm::DevBlocks block;            // holds the device arrays below
     int64_t W = 0;                  // words of 64 nodes per source (a multiple of kTile)
+    // (not on small grids:)
     uint16_t* list = nullptr;       // device [S][W / 64][4096] nodes of a tile to recompute
     int32_t* count = nullptr;       // device [S][W / 64] their number
     uint32_t* batch = nullptr;      // device [S][W] batches of 64 of them: tile * 64 + batch
@@ -78,6 +79,7 @@ constexpr int kThreads = 256;
 // 16 sources 3.9, 8.6 and 23.9 ms; 41x41x25, 1, 4 and 16 2.1, 3.8 and 8.5; 77x40, 3
 // sources 1.24 against 1.07 with k_eik_word.)
 constexpr int64_t kSmall2 = 8192, kSmall3 = 2048;
+bool is_small(int dim, int64_t words) { return words <= (dim == 3 ? kSmall3 : kSmall2); }
 constexpr uint16_t kCopy = 1u << 15;   // list entry: the value is only copied
 
 struct EikDims {
@@ -466,19 +468,18 @@ int fm_eikonal_create(int32_t dim, int64_t n1, int64_t n2, int64_t n3, const dou
     e->S = max_sources;
     e->stream = (hipStream_t)hip_stream;
     hipError_t h = hipGetDevice(&e->device);
-    const size_t nsn = (size_t)max_sources * (size_t)N;
-    if (h == hipSuccess) h = hipMalloc(&e->X, sizeof(double) * (size_t)N * dim);
-    if (h == hipSuccess) h = hipMalloc(&e->Tb, sizeof(double) * nsn);
     e->W = (N + 64 * kTile - 1) / (64 * kTile) * kTile;
-    const size_t src = (size_t)max_sources, W = (size_t)e->W;
+    const size_t src = (size_t)max_sources, W = (size_t)e->W, listed = is_small(dim, (int64_t)src * e->W) ? 0 : src * W;
     if (h == hipSuccess)
-        h = e->block.take({{(void**)&e->chg[0], sizeof(uint64_t) * src * W},
+        h = e->block.take({{(void**)&e->X, sizeof(double) * (size_t)N * dim},
+                           {(void**)&e->Tb, sizeof(double) * src * (size_t)N},
+                           {(void**)&e->chg[0], sizeof(uint64_t) * src * W},
                            {(void**)&e->chg[1], sizeof(uint64_t) * src * W},
                            {(void**)&e->seed, sizeof(uint64_t) * src * W},
                            {(void**)&e->edge, sizeof(uint64_t) * 4 * W},
-                           {(void**)&e->list, sizeof(uint16_t) * 64 * src * W},
-                           {(void**)&e->count, sizeof(int32_t) * src * (W / kTile)},
-                           {(void**)&e->batch, sizeof(uint32_t) * src * W},
+                           {(void**)&e->list, sizeof(uint16_t) * 64 * listed},
+                           {(void**)&e->count, sizeof(int32_t) * (listed / kTile)},
+                           {(void**)&e->batch, sizeof(uint32_t) * listed},
                            {(void**)&e->xi, sizeof(double) * 3 * src},
                            {(void**)&e->n_batch, sizeof(unsigned) * (kChunk + 1)}});
     int cus = 0;
@@ -547,7 +548,7 @@ int fm_eikonal_solve(fm_eikonal* e, const double* s, int32_t S, const double* xi
     const auto step_fn = e->dim == 3 ? k_eik_step<3> : k_eik_step<2>;
     const auto word_fn = e->dim == 3 ? k_eik_word<3> : k_eik_word<2>;
     const int64_t words = (int64_t)S * e->W;
-    const bool small = words <= (e->dim == 3 ? kSmall3 : kSmall2);
+    const bool small = is_small(e->dim, words);
     int cur = 0;
     int32_t done = 0;
     while (done < max_iter) {
@@ -592,8 +593,6 @@ int fm_eikonal_solve(fm_eikonal* e, const double* s, int32_t S, const double* xi
 
 void fm_eikonal_free(fm_eikonal* e) {
     if (!e) return;
-    if (e->X) (void)hipFree(e->X);
-    if (e->Tb) (void)hipFree(e->Tb);
     e->block.release();
     if (e->n_batch_h) (void)hipHostFree(e->n_batch_h);
     delete e;
