@@ -274,10 +274,10 @@ int fm_set_iterative_block_min(int32_t k_min);
  * Device scratch of about min(S, nthreads) x N x 91 bytes (at most ~2.3 GB),
  * pinned host staging of the same chunk x N x 58 bytes, per host thread
  * about 56 x N bytes of device memory and 18 x N bytes of pinned host
- * memory, and a recycled pool of per-source couplings (57 x N bytes each,
- * one per source in flight) are allocated and freed inside the call; each
- * state holds its records
- * (about 80 x N bytes) on the device from the call on.  Face stencil only (fm_grid.stencil
+ * memory, and, with more than nthreads sources, a recycled pool of per-source
+ * couplings (57 x N bytes each, one per source in flight) are allocated and
+ * freed inside the call; each state holds its records (about 80 x N bytes) on
+ * the device from the call on.  Face stencil only (fm_grid.stencil
  * 0 or 6, else FM_EINVAL).  Errors: as fm_build_frozen_states_w (a T that is
  * not finite or not 0 at the source gives FM_EINVAL); FM_EHIP for a failed
  * HIP call.

@@ -906,7 +906,11 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
         // the same in these vectors or, for the last chunk, in the staging
         const uint8_t *pm = nullptr, *pt = nullptr;
         const double *pw = nullptr, *pc = nullptr;
-        void* dev = nullptr;     // device copy of w [N][6], c [N], m [N] for the host thread's device work
+        // the same on the device for the host thread's device work: the last
+        // chunk's where they were computed, earlier ones copied to a block of the pool
+        const double *dw = nullptr, *dc = nullptr;
+        const uint8_t* dm = nullptr;
+        void* dev = nullptr;
     };
     std::vector<Couplings> buf(S);
     // device copies of the couplings, recycled between sources
@@ -949,14 +953,9 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
             pre.levels = device_levels;
             pre.pack = device_pack;
             pre.ctx = &lctx[id];
-            if (buf[a].dev) {
-                lctx[id].src_w6 = (const double*)buf[a].dev;
-                lctx[id].src_cal = lctx[id].src_w6 + (size_t)N * 6;
-                lctx[id].src_pm = (const uint8_t*)(lctx[id].src_cal + (size_t)N);
-            } else {
-                lctx[id].src_w6 = lctx[id].src_cal = nullptr;
-                lctx[id].src_pm = nullptr;
-            }
+            lctx[id].src_w6 = buf[a].dw;
+            lctx[id].src_cal = buf[a].dc;
+            lctx[id].src_pm = buf[a].dm;
             fm_state* stt = nullptr;
             const int r = build_state(g, nullptr, s, src_nodes[a],
                                       n_rcv > 0 ? rcv_nodes + (size_t)a * per_src : nullptr,
@@ -1032,11 +1031,13 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
             msg = std::string("GPU setup pass failed: ") + hipGetErrorString(e);
             break;
         }
+        const bool last = a0 + chunk >= S;
         // each source's couplings stay on the device for its host thread
-        // (their device work then needs no upload); without the memory for
-        // it the host thread uploads them
+        // (their device work then needs no upload): the last chunk's where
+        // they are, since nothing overwrites them; without the memory for a copy
+        // of earlier ones the host thread uploads them
         const size_t copy = ((size_t)N * (6 * sizeof(double) + sizeof(double) + 1) + 255) & ~size_t(255);
-        if (a0 == 0 && copy > (size_t(2) << 20)) {      // (devmem.h)
+        if (a0 == 0 && !last && copy > (size_t(2) << 20)) {      // (devmem.h)
             void* p = nullptr;
             if (hipMalloc(&p, copy * (size_t)n) == hipSuccess) {
                 std::lock_guard<std::mutex> lk(pool_mu);
@@ -1046,7 +1047,12 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
                 (void)hipGetLastError();
             }
         }
-        for (int32_t k = 0; k < n && e == hipSuccess; k++) {
+        for (int32_t k = 0; k < n && last; k++) {
+            buf[a0 + k].dw = dw + (size_t)k * N * 6;
+            buf[a0 + k].dc = dc + (size_t)k * N;
+            buf[a0 + k].dm = dm + (size_t)k * N;
+        }
+        for (int32_t k = 0; k < n && !last && e == hipSuccess; k++) {
             void* p = nullptr;
             {
                 std::lock_guard<std::mutex> lk(pool_mu);
@@ -1064,6 +1070,9 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
                 pool_all.push_back(p);
             }
             buf[a0 + k].dev = p;
+            buf[a0 + k].dw = (const double*)p;
+            buf[a0 + k].dc = buf[a0 + k].dw + (size_t)N * 6;
+            buf[a0 + k].dm = (const uint8_t*)(buf[a0 + k].dc + N);
             e = hipMemcpyAsync(p, dw + (size_t)k * N * 6, sizeof(double) * 6 * (size_t)N, hipMemcpyDeviceToDevice, st);
             if (e == hipSuccess)
                 e = hipMemcpyAsync((double*)p + (size_t)N * 6, dc + (size_t)k * N, sizeof(double) * (size_t)N,
@@ -1071,11 +1080,10 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
             if (e == hipSuccess)
                 e = hipMemcpyAsync((double*)p + (size_t)N * 7, dm + (size_t)k * N, (size_t)N, hipMemcpyDeviceToDevice, st);
         }
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess && !last) e = hipStreamSynchronize(st);
         // the next chunk's device work runs while this one is copied out of
         // the staging (one host thread per source); nothing overwrites the last
         // chunk's, which is read where it is (24 ms for 8 sources on 101x101x51)
-        const bool last = a0 + chunk >= S;
         if (e == hipSuccess && !last) e = launch_chunk(a0 + chunk);
         auto hand_over = [&](int32_t k) {
             Couplings& cp = buf[a0 + k];
