@@ -12,20 +12,24 @@ struct Part {
     size_t bytes;
 };
 
-// An array of up to 2 MB is an allocation of its own, which the runtime takes
-// from its pool (1 us, 1 us to free); the larger ones are one allocation
-// together, since each would cost 270 us from 4 MB on, one at a time whichever
-// thread asks.  (All in one, 18 arrays of 42,000 nodes cost 360 us where 115 do;
-// each alone, 8 sources on 101x101x51 spent 54 of 165 ms in 215 frees.)
+// Arrays of up to 2 MB, 4 MB of them together, are allocations of their own,
+// which the runtime takes from its pool (1 us each, 1 us to free); all others are
+// one allocation, since each costs 270 us from 4 MB on, one at a time whichever
+// thread asks, and the pool grows by chunks of 2 MB at a cost of their own.
+// (All in one, 18 arrays of 42,000 nodes cost 360 us where 115 do; all alone,
+// 8 sources on 101x101x51 spent 54 of 165 ms in 215 frees; up to 2 MB alone without
+// the second limit, one source on 112x42x33 took 14.1 ms for 13.0.)
 struct DevBlocks {
     std::vector<void*> blocks;
 
     hipError_t take(const std::vector<Part>& parts) {
-        constexpr size_t kPool = size_t(2) << 20;
         auto whole = [](size_t n) { return (n + 255) & ~size_t(255); };
+        size_t small = 0;
+        for (const Part& x : parts) small += x.bytes > kAlone ? 0 : whole(x.bytes);
+        const size_t alone = small > 2 * kAlone ? 0 : kAlone;
         size_t rest = 0;
         for (const Part& x : parts) {
-            if (x.bytes > kPool) {
+            if (x.bytes > alone) {
                 rest += whole(x.bytes);
                 continue;
             }
@@ -38,7 +42,7 @@ struct DevBlocks {
         if (e != hipSuccess) return e;
         char* at = (char*)block;
         for (const Part& x : parts)
-            if (x.bytes > kPool) {
+            if (x.bytes > alone) {
                 *x.p = at;
                 at += whole(x.bytes);
             }
@@ -49,6 +53,8 @@ struct DevBlocks {
         for (void* p : blocks) (void)hipFree(p);
         blocks.clear();
     }
+
+    static constexpr size_t kAlone = size_t(2) << 20;
 
 private:
     hipError_t add(void** p, size_t bytes) {

@@ -1037,7 +1037,7 @@ extern "C" int fm_build_frozen_states_gpu(const fm_grid* g, int32_t S, const dou
         // they are, since nothing overwrites them; without the memory for a copy
         // of earlier ones the host thread uploads them
         const size_t copy = ((size_t)N * (6 * sizeof(double) + sizeof(double) + 1) + 255) & ~size_t(255);
-        if (a0 == 0 && !last && copy > (size_t(2) << 20)) {      // (devmem.h)
+        if (a0 == 0 && !last && copy > DevBlocks::kAlone) {
             void* p = nullptr;
             if (hipMalloc(&p, copy * (size_t)n) == hipSuccess) {
                 std::lock_guard<std::mutex> lk(pool_mu);
